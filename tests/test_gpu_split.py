@@ -274,3 +274,29 @@ def test_three_stage_few_tiles_large_kernels():
         p.run(xd, wd, y)
         torch.cuda.synchronize()
     assert_close(y.cpu().numpy(), direct_conv(x, w), 7, "three_stage F(7), few tiles")
+
+
+# (shape, m): one image, output channels of a task missing (the epilogue's rounds of 8
+# channels past K begin past the end of y), and images lower than a tile (so do its rows)
+FEW_CHANNELS = [((1, 32, 40, 256, 257), 4), ((1, 32, 40, 250, 251), 2), ((1, 32, 24, 350, 351), 5), ((1, 32, 20, 400, 399), 6),
+                ((1, 17, 57, 1, 16390), 4), ((1, 17, 57, 1, 8190), 2), ((1, 17, 25, 1, 20003), 5), ((1, 17, 25, 1, 24003), 6),
+                ((1, 17, 57, 2, 16390), 4), ((1, 17, 25, 2, 24003), 6)]
+
+
+@pytest.mark.parametrize("case", FEW_CHANNELS, ids=_id)
+def test_split_kernel_few_output_channels(case):
+    """Layers of one image and fewer output channels than a task holds: parity, and nothing
+    written within 64 planes around y."""
+    (N, C, K, H, W), m = case
+    x, w, xd, wd = _device(case[0], 200 + m + sum(case[0]))
+    print(f"\n[gpu] few channels {_id(case)}", flush=True)
+    n, pad = K * H * W, 64 * H * W
+    buf = torch.full((n + 2 * pad,), float("nan"), device="cuda")
+    y = buf[pad:pad + n].view(N, K, H, W)
+    with wc.Plan(N, C, K, H, W, m) as p:
+        assert "split products" in p.describe(), p.describe()
+        p.run(xd, wd, y)
+        p.status()
+    torch.cuda.synchronize()
+    assert torch.isnan(buf[:pad]).all() and torch.isnan(buf[pad + n:]).all()
+    assert_close(y.cpu().numpy(), direct_conv(x, w), m, _id(case))
