@@ -46,8 +46,15 @@ __device__ float fft_buffer_load_f32(fft_int32x4 rsrc, unsigned voffset, unsigne
     __asm("llvm.amdgcn.raw.buffer.load.f32");
 __device__ fft_floatx4 fft_buffer_load_f32x4(fft_int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.load.v4f32");
-__device__ void fft_buffer_store_f32x4(fft_floatx4 v, fft_int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
+__device__ void fft_raw_buffer_store_f32x4(fft_floatx4 v, fft_int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.store.v4f32");
+// The next instruction must not overwrite the data registers of a store of more than 64
+// bits; the compiler does not see to it where the scalar offset is in a register.
+__device__ __forceinline__ void fft_buffer_store_f32x4(fft_floatx4 v, fft_int32x4 rsrc, unsigned voffset, unsigned soffset,
+                                                       int aux) {
+    fft_raw_buffer_store_f32x4(v, rsrc, voffset, soffset, aux);
+    asm volatile("s_nop 0" ::"v"(v));
+}
 __device__ void fft_buffer_store_f32(float v, fft_int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.store.f32");
 

@@ -63,8 +63,17 @@ __device__ floatx2 buffer_load_f32x2(int32x4 rsrc, unsigned voffset, unsigned so
     __asm("llvm.amdgcn.raw.buffer.load.v2f32");
 __device__ floatx4 buffer_load_f32x4(int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.load.v4f32");
-__device__ void buffer_store_f32x4(floatx4 v, int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
+__device__ void raw_buffer_store_f32x4(floatx4 v, int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.store.v4f32");
+// A store of more than 64 bits reads its data registers after it has issued: the next
+// instruction must not overwrite them.  The compiler sees to that only where the scalar
+// offset is a constant; with one in a register the stored value was the overwriting one now
+// and then.  The data stay in use past one idle cycle.
+__device__ __forceinline__ void buffer_store_f32x4(floatx4 v, int32x4 rsrc, unsigned voffset, unsigned soffset,
+                                                   int aux) {
+    raw_buffer_store_f32x4(v, rsrc, voffset, soffset, aux);
+    asm volatile("s_nop 0" ::"v"(v));
+}
 __device__ void buffer_store_f32x2(floatx2 v, int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.store.v2f32");
 __device__ void buffer_store_f32(float v, int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
