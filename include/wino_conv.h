@@ -113,10 +113,12 @@ enum {
  * for it; it takes 32 tiles x 64 output channels (m = 5, 6: 32) and 16 input channels
  * at a time.  wino_conv_describe
  * names the kernel a plan runs.  Its results are those of the fp32 kernel to fp32
- * rounding, except that an infinite input or kernel reaches the outputs as NaN, that
- * transformed values of 3.39e38 and more (the largest bf16) count as infinite, and
- * that terms below 2^-126 count as zero: inputs below about 2^-108 lose low bits
- * (relative error 3e-6 at 2^-116). */
+ * rounding over the whole range of float: values are multiplied at a scale that keeps
+ * all terms of the smallest, denormal ones included, and output tiles whose sums
+ * leave the scaled range (transformed values of 2^102 and more, sums of products of
+ * 2^80 and more, infinities, NaNs) are computed again as fp32 products, which takes
+ * many times as long for those tiles.  The same holds for the three-stage products,
+ * which most layers of 64 and more channels form that way. */
 #define WINO_MAX_CHANNEL_SPLITS 64
 typedef struct {
     int tiles_per_wg;

@@ -83,6 +83,24 @@ void describe_fused(const Geometry &g, const FusedCfg &cfg, char *buf, size_t le
 hipError_t launch_weight_transform(const Geometry &g, const float *w, float *wt, hipStream_t s,
                                    unsigned *zero = nullptr, int nzero = 0);
 
+// Split products: a value is multiplied as three bf16 terms that add up to it.  bf16 has
+// float's exponents, so the low terms of small values would run out of them; both factors
+// are therefore taken times 2^24 (exact), which makes every term of every float, denormal
+// ones included, a normal bf16, and results are divided by the product of the scales.
+constexpr float kSplitScale = 16777216.0f, kSplitUnscale = 1.0f / kSplitScale / kSplitScale;
+// Transformed kernels of this magnitude and more, infinite ones and NaNs have no finite
+// scaled terms: they are held as a NaN first term, which makes every sum they enter NaN,
+// and their own 32 bits in the other two (high half first).
+constexpr float kSplitMax = 0x1p102f;
+constexpr unsigned kSplitRaw = 0x7fff;
+// The float behind a transformed kernel's terms.
+__host__ __device__ inline float split_value(unsigned t0, unsigned t1, unsigned t2) {
+    const float a = __builtin_bit_cast(float, t0 << 16), b = __builtin_bit_cast(float, t1 << 16);
+    const float c = __builtin_bit_cast(float, t2 << 16);
+    const float sum = ((t1 | t2) & 0x7fff) == 0 ? a : (a + b) + c;  // (a: keeps the sign of a zero)
+    return t0 == kSplitRaw ? __builtin_bit_cast(float, t1 << 16 | t2) : sum * (1.0f / kSplitScale);
+}
+
 // The same as three bf16 terms per value in the operand order of the split-product
 // kernels, [kb = k/32][cs = c/16][f][term][lane = (c%16)/8*32 + k%32][c%8] bf16, kb
 // up to a multiple of 64 output channels, zeros past C and K.
@@ -91,8 +109,8 @@ hipError_t launch_weight_transform_split(const Geometry &g, const float *w, floa
 inline size_t split_weight_bytes(const Geometry &g) {
     return (size_t)(g.Kb_alloc / 2) * ((g.C + 15) / 16) * g.T2 * 3072;
 }
-// Host copy of that buffer back to floats in the order launch_weight_transform
-// writes ([Kb][Cs][Q][64][4]); the sum of the three terms is the float they came from.
+// Host copy of that buffer back to the floats it holds, in the order launch_weight_transform
+// writes ([Kb][Cs][Q][64][4]).
 void unsplit_weights(const Geometry &g, const unsigned short *split, float *out, size_t count);
 
 // Fused: x -> y with the transformed kernels wt.

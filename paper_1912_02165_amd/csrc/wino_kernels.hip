@@ -5,7 +5,6 @@
 #include "wino_split.h"
 
 #include <cstdio>
-#include <cstring>
 
 namespace wino {
 
@@ -79,8 +78,14 @@ __device__ __forceinline__ void weight_split_part(const float *gk, unsigned shor
     const int c = tid & 15, k = tid >> 4, at = ((c >> 3) * 32 + k) * 8 + (c & 7);
 #pragma unroll
     for (int f = 0; f < FN; ++f) {
+        const float v = t[F0 + f];
         unsigned a, b, e;
-        split_pair(t[F0 + f], 0.0f, a, b, e);
+        split_pair(v * kSplitScale, 0.0f, a, b, e);
+        if (!(__builtin_fabsf(v) < kSplitMax)) {
+            a = kSplitRaw;
+            b = __builtin_bit_cast(unsigned, v) >> 16;
+            e = __builtin_bit_cast(unsigned, v);
+        }
         st[f * 1536 + at] = (unsigned short)a;
         st[f * 1536 + 512 + at] = (unsigned short)b;
         st[f * 1536 + 1024 + at] = (unsigned short)e;
@@ -262,11 +267,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // it needs); also a compiler barrier, so no LDS access moves across it.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
-// A copy of v in a register of its own, so that loads into v's can be issued and a loop
-// needs no copies (and waits for them) at its end.
-__device__ __forceinline__ float taken(float v) {
+// v at the scale of the split products, in a register of its own, so that loads into v's
+// can be issued and a loop needs no copies (and waits for them) at its end.
+__device__ __forceinline__ float taken_scaled(float v) {
     float r;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
+    asm volatile("v_mul_f32 %0, %1, %2" : "=v"(r) : "s"(kSplitScale), "v"(v));
     return r;
 }
 
@@ -435,7 +440,8 @@ __global__ void __launch_bounds__(256, 3) frequency_gemm_split_kernel(const floa
         for (int i = 0; i < 2; ++i)
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
-                r[i][q] = floatx4{taken(raw[4 * q][i]), taken(raw[4 * q + 1][i]), taken(raw[4 * q + 2][i]), taken(raw[4 * q + 3][i])};
+                r[i][q] = floatx4{taken_scaled(raw[4 * q][i]), taken_scaled(raw[4 * q + 1][i]), taken_scaled(raw[4 * q + 2][i]),
+                                  taken_scaled(raw[4 * q + 3][i])};
             }
         // past the end the last step's copies and loads again: nobody reads them
         const int nx = st + 1 < steps ? st + 1 : st;
@@ -467,14 +473,49 @@ __global__ void __launch_bounds__(256, 3) frequency_gemm_split_kernel(const floa
     // the copies issued with the last step must land before the workgroup ends and its
     // LDS can be given to another workgroup
     wait_vmcnt<0>();
-    const int tile = 32 * th + (lane & 31);
+    const int tb = tg * 4 + 2 * th + ((lane >> 4) & 1);
+    // M of the lane's element v of output block k
+    auto out = [&](int k, int v) {
+        const int kb16 = kg * 4 + 2 * k + v / 8, l16 = (2 * ((v / 4) & 1) + (lane >> 5)) * 16 + (lane & 15);
+        return Mout + (((((long long)f4 * TB + tb) * g.Kb_alloc + kb16) * 4 + v % 4) * 64 + l16) * 4 + 2 * fp;
+    };
+    // a frequency past T^2 (the wave's second one only) is zero, whatever the kernels repeated for it hold
+    const int f0 = 4 * f4 + 2 * fp, nf = T2 - f0 < 2 ? (T2 - f0 < 0 ? 0 : T2 - f0) : 2;
+    float sum = 0.0f;  // of the results: not finite if one of them is not
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int kb16 = kg * 4 + 2 * k + v / 8, l16 = (2 * ((v / 4) & 1) + (lane >> 5)) * 16 + (lane & 15);
-            float *dst = Mout + (((((long long)f4 * TB + tg * 4 + tile / 16) * g.Kb_alloc + kb16) * 4 + v % 4) * 64 + l16) * 4 + 2 * fp;
-            *reinterpret_cast<floatx2 *>(dst) = floatx2{acc[0][k][v], acc[1][k][v]};
+            floatx2 r;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                r[i] = i < nf ? acc[i][k][v] * kSplitUnscale : 0.0f;
+                sum += acc[i][k][v];
+            }
+            *reinterpret_cast<floatx2 *>(out(k, v)) = r;
+        }
+    // Sums beyond the scaled range (or of infinities) again, as fp32 products: the lane's
+    // element of each of its tiles' frequencies straight from U and the kernels.
+    if (__builtin_amdgcn_ballot_w64(!finite(sum)) == 0) return;
+    unsigned again[2] = {0u, 0u};  // bit 16 k + v
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int n = 0; n < 32; ++n) again[i] |= (i < nf && !finite(acc[i][n / 16][n % 16])) ? 1u << n : 0u;
+    const float *ub = U + (((long long)f4 * TB + tb) * Cs * 64 + (lane & 15)) * 4 + 2 * fp;
+    for (int i = 0; i < 2; ++i)
+        for (int n = 0; n < 32; ++n) {
+            if (!((again[i] >> n) & 1u)) continue;
+            const int k = kg * 64 + (n / 16) * 32 + ((n % 16) / 8) * 16 + (2 * ((n / 4) & 1) + (lane >> 5)) * 4 + n % 4;
+            float m = 0.0f;
+            for (int cs = 0; cs < Cs * 4; cs += 16) {  // 16 channels on their own, as the matrix products add them
+                float part = 0.0f;
+                for (int c = cs; c < Cs * 4 && c < cs + 16; ++c)
+                    part = __builtin_fmaf(split_kernel_value<M>(wt, steps, k, c, f0 + i),
+                                          ub[((c >> 2) * 64 + (c & 3) * 16) * 4 + i], part);
+                m += part;
+            }
+            out(n / 16, n % 16)[i] = m;
         }
 }
 
@@ -565,12 +606,6 @@ hipError_t launch_weight_transform_split(const Geometry &g, const float *w, floa
 
 void unsplit_weights(const Geometry &g, const unsigned short *split, float *out, size_t count) {
     const int cs16 = (g.C + 15) / 16, Q = (g.T2 + 3) / 4;
-    auto term = [](unsigned short v) {
-        const unsigned u = (unsigned)v << 16;
-        float f;
-        std::memcpy(&f, &u, sizeof f);
-        return f;
-    };
     for (size_t i = 0; i < count; ++i) {
         const int f4 = (int)(i & 3), lane = (int)(i >> 2 & 63);
         const size_t grp = i >> 8;
@@ -582,7 +617,7 @@ void unsplit_weights(const Geometry &g, const unsigned short *split, float *out,
         }
         const unsigned short *p = split + (((size_t)(k / 32) * cs16 + c / 16) * g.T2 + f) * 1536 +
                                   ((c % 16 / 8) * 32 + k % 32) * 8 + c % 8;
-        out[i] = (term(p[0]) + term(p[512])) + term(p[1024]);
+        out[i] = split_value(p[0], p[512], p[1024]);
     }
 }
 

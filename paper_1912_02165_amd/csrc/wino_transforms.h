@@ -234,6 +234,73 @@ __device__ __forceinline__ void bt_1d(const float *in, float *out) {
     }
 }
 
+// k times dot_unit_first, k a power of two (so the same bits): the first term is a
+// multiplication, the others take k into their coefficients.  Where two coefficients are
+// +-1 the first term is the second of them (SECOND) or the first: the choice under which
+// the sums of bt_1d_scaled share the most first terms.
+template <int T, int SI, int A0, int DA, bool SECOND>
+__device__ __forceinline__ float dot_unit_first_scaled(const float (&c)[T], const float *in, float k, float sc = 1.0f) {
+    int u1 = -1, u2 = -1;  // the first two with a coefficient of +-1
+#pragma unroll
+    for (int a = A0; a < T; a += DA) {
+        const float cf = c[a] / sc;
+        if (cf != 1.0f && cf != -1.0f) continue;
+        if (u1 < 0) u1 = a;
+        else if (u2 < 0) u2 = a;
+    }
+    const int f1 = SECOND && u2 >= 0 ? u2 : u1, f2 = SECOND && u2 >= 0 ? u1 : u2;
+    float acc = 0.f;
+    bool first = true;
+#pragma unroll
+    for (int pass = 0; pass < 4; ++pass) {
+#pragma unroll
+        for (int a = A0; a < T; a += DA) {
+            const float cf = c[a] / sc;
+            const bool unit = cf == 1.0f || cf == -1.0f;
+            const int at = a == f1 ? 0 : a == f2 ? 1 : unit ? 2 : 3;
+            if (at != pass || cf == 0.0f) continue;
+            if (first) {
+                const float v = k * in[a * SI];
+                acc = cf == 1.0f ? v : cf == -1.0f ? -v : cf * v;
+                first = false;
+            } else {
+                acc = __builtin_fmaf(cf * k, in[a * SI], acc);
+            }
+        }
+    }
+    return acc;
+}
+
+// out[i*SO] = k * sum_a B^T[i][a] in[a*SI], i, a < T: bt_1d with the scale k, a power of two
+// (so the same bits), at 2 to 4 more multiplications for all rows.
+template <int M, int SI, int SO>
+__device__ __forceinline__ void bt_1d_scaled(const float *in, float *out, float k) {
+    constexpr Tables<M> tb{};
+    constexpr HalfScale<M> hs{};
+    constexpr int T = M + 2;
+    constexpr bool neg = pair_sign<M>() < 0.0f;
+    if constexpr (pair0<M>() == 1) out[0] = dot_unit_first_scaled<T, SI, 0, 1, true>(tb.bt[0], in, k);
+    out[(T - 1) * SO] = dot_unit_first_scaled<T, SI, 0, 1, false>(tb.bt[T - 1], in, k);
+#pragma unroll
+    for (int j = pair0<M>(); j + 1 < T - 1; j += 2) {
+        const float se = hs.s[j][0], so = hs.s[j][1];
+        const float e0 = dot_unit_first_scaled<T, SI, 0, 2, true>(tb.bt[j], in, k, se);
+        const float o0 = dot_unit_first_scaled<T, SI, 1, 2, true>(tb.bt[j], in, k, so);
+        const float e = (se != 1.0f && so != 1.0f) ? se * e0 : e0;
+        const float es = (se != 1.0f && so != 1.0f) ? 1.0f : se;
+        if (es == 1.0f && so == 1.0f) {
+            out[j * SO] = e + o0;
+            out[(j + 1) * SO] = neg ? o0 - e : e - o0;
+        } else if (es == 1.0f) {
+            out[j * SO] = __builtin_fmaf(so, o0, e);
+            out[(j + 1) * SO] = neg ? __builtin_fmaf(so, o0, -e) : __builtin_fmaf(-so, o0, e);
+        } else {
+            out[j * SO] = __builtin_fmaf(es, e, o0);
+            out[(j + 1) * SO] = neg ? __builtin_fmaf(-es, e, o0) : __builtin_fmaf(es, e, -o0);
+        }
+    }
+}
+
 // out[i*SO] = sum_j A^T[i][j] in[j*SI], i < M, j < T.
 template <int M, int SI, int SO>
 __device__ __forceinline__ void at_1d(const float *in, float *out) {
@@ -255,6 +322,37 @@ __device__ __forceinline__ void at_1d(const float *in, float *out) {
 #pragma unroll
         for (int q = 0; q < NP; ++q) mac(acc, first, tb.at[i][J0 + 2 * q], (i % 2 == 0) ? s[q] : d[q]);
         mac(acc, first, tb.at[i][T - 1], in[(T - 1) * SI]);
+        out[i * SO] = acc;
+    }
+}
+
+// out[i*SO] = k * sum_j A^T[i][j] in[j*SI], i < M, j < T: at_1d with the scale k (a power of
+// two, so the same bits) in its coefficients: two multiplications for all rows, as the
+// first pair's sum and difference start every row with a coefficient of 1.  An input that is
+// not finite, or a sum of a pair that overflows, makes out[0] or out[(M-1)*SO] not finite
+// (odd M: or out[SO]).
+template <int M, int SI, int SO>
+__device__ __forceinline__ void at_1d_scaled(const float *in, float *out, float k) {
+    constexpr Tables<M> tb{};
+    constexpr int T = M + 2;
+    constexpr int J0 = pair0<M>();
+    constexpr int NP = (T - 1 - J0) / 2;  // number of (+p, -p) pairs
+    static_assert(tb.at[0][J0] == 1.0f && tb.at[1][J0] == 1.0f, "the first pair is +-1");
+    float s[NP], d[NP];
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+        s[q] = in[(J0 + 2 * q) * SI] + in[(J0 + 1 + 2 * q) * SI];
+        d[q] = in[(J0 + 2 * q) * SI] - in[(J0 + 1 + 2 * q) * SI];
+    }
+    const float s0 = k * s[0], d0 = k * d[0];
+#pragma unroll
+    for (int i = 0; i < M; ++i) {
+        float acc = (i % 2 == 0) ? s0 : d0;
+        if constexpr (J0 == 1)
+            if (tb.at[i][0] != 0.0f) acc = __builtin_fmaf(tb.at[i][0] * k, in[0], acc);
+#pragma unroll
+        for (int q = 1; q < NP; ++q) acc = __builtin_fmaf(tb.at[i][J0 + 2 * q] * k, (i % 2 == 0) ? s[q] : d[q], acc);
+        if (tb.at[i][T - 1] != 0.0f) acc = __builtin_fmaf(tb.at[i][T - 1] * k, in[(T - 1) * SI], acc);
         out[i * SO] = acc;
     }
 }

@@ -300,3 +300,116 @@ def test_split_kernel_few_output_channels(case):
     torch.cuda.synchronize()
     assert torch.isnan(buf[:pad]).all() and torch.isnan(buf[pad + n:]).all()
     assert_close(y.cpu().numpy(), direct_conv(x, w), m, _id(case))
+
+
+# ---- the whole range of float -------------------------------------------------
+
+def _run_pair(shape, m, algo, xd, wd):
+    """y of the split products and of the fp32 products of the same transforms."""
+    blocking = {"tiles_per_wg": 32 if m == 2 else 16, "k_per_wg": 64 if m <= 4 else 32}
+    ys = []
+    for a, tuning in ((algo, None), ("fused", {"channel_splits": 2, **blocking})):
+        y = torch.full((shape[0], shape[2], *shape[3:]), 7.0, device="cuda")
+        with wc.Plan(*shape, m, a, tuning) as p:
+            assert ("split" in p.describe().split("split items")[0]) == (tuning is None), p.describe()
+            p.run(xd, wd, y)
+            p.status()
+        ys.append(y.cpu().numpy())
+    return ys
+
+
+# (m, algorithm, shape): whole items, items in pieces, the three-stage products
+RANGE = [(m, "fused", (20, 64, 64, 46, 46)) for m in (2, 4, 5, 6)] + [
+    (2, "fused", (25, 128, 65, 17, 13)), (4, "fused", (35, 250, 200, 13, 15)), (5, "fused", (28, 250, 128, 13, 15)),
+    (6, "fused", (30, 250, 128, 13, 15))] + [(m, "three_stage", (20, 70, 66, 13, 15)) for m in (2, 4, 5, 6)]
+
+
+def _range_id(c):
+    return "m%d-%s-%s" % (c[0], c[1], "x".join(map(str, c[2])))
+
+
+@pytest.mark.parametrize("side", ("input", "kernels"))
+@pytest.mark.parametrize("case", RANGE, ids=_range_id)
+def test_split_products_keep_small_and_large_values(case, side):
+    """Images (or output channels) at binary orders of magnitude from 2^-145 (denormal) to 2^120,
+    the other factor scaled so that the results stay normal: the error of each against fp64
+    within 1.5 times that of the fp32 products.  These add two halves of the channels, so
+    their error may be smaller than that of one sum by sqrt(2); the rest is for chance in one
+    image or channel.  (Denormal factors are compared with the fp64 result of the values they
+    round to.)"""
+    m, algo, shape = case
+    N, C, K, H, W = shape
+    x, w, _, _ = _device(shape, 50 + m + C)
+    for exps, other in ((np.linspace(-145, -96, N if side == "input" else K), 60), (np.linspace(60, 120, N if side == "input" else K), -60)):
+        sc = np.exp2(np.round(exps))
+        if side == "input":
+            xs, ws = (x * sc[:, None, None, None]).astype(np.float32), (w * 2.0 ** other).astype(np.float32)
+        else:
+            xs, ws = (x * 2.0 ** other).astype(np.float32), (w * sc[:, None, None, None]).astype(np.float32)
+        ref = direct_conv(xs.astype(np.float64), ws.astype(np.float64))
+        ys = _run_pair(shape, m, algo, torch.from_numpy(xs).cuda(), torch.from_numpy(ws).cuda())
+        axis = 0 if side == "input" else 1
+        rel = np.array([[errors(np.take(y, i, axis), np.take(ref, i, axis))[0] for i in range(len(sc))] for y in ys])
+        print(f"{_range_id(case)} {side} {other}: worst {rel[0].max():.3e} fp32 {rel[1].max():.3e} "
+              f"ratio {(rel[0] / rel[1]).max():.3f}")
+        assert np.isfinite(ys[0]).all() and (rel[0] <= 1.5 * rel[1]).all(), rel
+
+
+@pytest.mark.parametrize("case", RANGE, ids=_range_id)
+def test_split_products_infinities_as_fp32(case):
+    """Infinities, NaNs and values beyond the scaled terms among the inputs and kernels: the same
+    outputs are infinite, with the same sign, and NaN as with the fp32 products, and the
+    images and channels without such values are not touched."""
+    m, algo, shape = case
+    N, C, K, H, W = shape
+    x, w, xd, wd = _device(shape, 70 + m + C)
+    for values, kernels in (((np.inf, 1e33, -np.inf, -1e32), ()), ((1e33, -1e33), (np.inf, np.nan, -np.inf)), ((), (1e33, -1e32))):
+        xs, ws = x.copy(), w.copy()
+        for i, v in enumerate(values):
+            xs[(3 * i) % N, (5 * i + 1) % C, (7 * i) % H, (4 * i + 2) % W] = v
+        for i, v in enumerate(kernels):
+            ws[(9 * i + 2) % K, (3 * i) % C, i, 2 - i] = v
+        a, b = _run_pair(shape, m, algo, torch.from_numpy(xs).cuda(), torch.from_numpy(ws).cuda())
+        assert np.array_equal(np.isnan(a), np.isnan(b)), (np.isnan(a).sum(), np.isnan(b).sum())
+        assert np.array_equal(np.isposinf(a), np.isposinf(b)) and np.array_equal(np.isneginf(a), np.isneginf(b))
+        assert np.isfinite(b).all() == (values == ())
+        # images and output channels without such a value
+        n = [i for i in range(N) if i not in [(3 * j) % N for j in range(len(values))]]
+        k = [i for i in range(K) if i not in [(9 * j + 2) % K for j in range(len(kernels))]]
+        a, b = a[n][:, k], b[n][:, k]
+        assert np.isfinite(a).all() and errors(a, b)[0] <= 2e-5
+
+
+def test_split_weights_read_back_any_value():
+    """Transformed kernels read back bit for bit, whatever their magnitude: denormal, beyond the
+    scaled terms, infinite, NaN, zeros of both signs."""
+    N, C, K, H, W = 8, 17, 130, 47, 61
+    w = np.random.default_rng(9).standard_normal((K, C, 3, 3)).astype(np.float32)
+    w *= np.exp2(np.random.default_rng(8).integers(-149, 128, size=(K, C, 1, 1))).astype(np.float32)
+    w[0, 0] = -0.0
+    w[1, 1, 0, 0] = np.inf
+    w[2, 2, 1, 1] = np.nan
+    w[3, 3, 2, 2] = np.finfo(np.float32).max
+    wd = torch.from_numpy(w).cuda()
+    got = []
+    for algo in ("fused", "three_stage"):
+        with wc.Plan(N, C, K, H, W, 4, algo) as p:
+            assert ("split products" in p.describe()) == (algo == "fused")
+            p.set_weights(wd)
+            got.append(p.intermediate(wc.WINO_BUF_WEIGHTS))
+    nan = np.isnan(got[1])
+    assert np.array_equal(np.isnan(got[0]), nan)
+    assert np.array_equal(got[0].view(np.uint32)[~nan], got[1].view(np.uint32)[~nan])
+
+
+def test_three_stage_padding_frequencies_zero():
+    """Frequencies past T^2 hold zeros in M whatever the kernels hold (F(5): 49 of 52)."""
+    shape = (1, 64, 16, 9, 9)
+    x, w, xd, wd = _device(shape, 5)
+    wd[3, 5, 1, 1] = float("inf")
+    y = torch.empty((1, 16, 9, 9), device="cuda")
+    with wc.Plan(*shape, 5, "three_stage") as p:
+        p.run(xd, wd, y)
+        M = _unfold(p.intermediate(wc.WINO_BUF_PRODUCT), "M")
+    assert np.isnan(M[:49]).any() or np.isinf(M[:49]).any()
+    assert not M[49:].any()
