@@ -150,7 +150,7 @@ def per_call_ms(timed, steps, exact=False):
     return timed(n) / n
 
 
-def time_pair(layer, m, algo, steps, warmup, x, w, per_call=False, tuning=None, exact=False):
+def time_pair(layer, m, algo, steps, warmup, x, w, per_call=False, tuning=None, exact=False, plan=None):
     """Time `steps` steps; returns dict with ms_per_step and the transform-domain
     kernel's average duration (ms) measured between events on the same stream.
     Every back-to-back timing covers at least MIN_TIMED_MS of GPU time (more calls
@@ -158,13 +158,14 @@ def time_pair(layer, m, algo, steps, warmup, x, w, per_call=False, tuning=None, 
     weigh on the mean), except the whole steps when `exact` is set: those are then
     exactly `steps` calls.
     per_call: also the median time of single calls, warm and cold (after a 512 MB
-    scratch write that evicts L2 and the 256 MB Infinity Cache)."""
+    scratch write that evicts L2 and the 256 MB Infinity Cache).
+    plan: the plan to time (closed here) instead of one of m, algo and tuning."""
     import torch
     import paper_1912_02165_amd as wc
     N, C, K, H, W = layer.N, layer.C, layer.K, layer.H, layer.W
     y = torch.empty((N, K, H, W), dtype=torch.float32, device="cuda")
     stream = torch.cuda.current_stream()
-    with wc.Plan(N, C, K, H, W, m, algo, tuning) as p:
+    with plan or wc.Plan(N, C, K, H, W, m, algo, tuning) as p:
         settle(lambda: p.run(x, w, y))
         for _ in range(warmup):
             p.run(x, w, y)
@@ -294,8 +295,8 @@ def layer_table(steps=20, warmup=10):
 
 def tuned_table(steps=20, warmup=10):
     """Per configured layer, the tile size, algorithm and blocking the per-layer
-    tuning picks (`wino_conv_plan_tuned` over every built fused blocking at F(2),
-    F(4), F(5), F(6) and the three-stage pipeline at those and F(7)), timed like
+    tuning picks (`wino_conv_plan_tuned` over every built fused blocking and the
+    split-product kernel (blocking 0 x 0) at F(2), F(4), F(5), F(6) and the three-stage pipeline at those and F(7)), timed like
     the pairs of `layer_table`."""
     import torch
     import paper_1912_02165_amd as wc
@@ -308,9 +309,7 @@ def tuned_table(steps=20, warmup=10):
         tp = wc.Plan.tuned(lay.N, lay.C, lay.K, lay.H, lay.W, wc.WINO_TUNE_ALL_M | wc.WINO_TUNE_THREE_STAGE)
         m, algo = tp.m, tp.algo
         _, _, R, kit = tp.params()
-        tp.close()
-        tuning = {"tiles_per_wg": R, "k_per_wg": kit} if algo == "fused" else None
-        r = time_pair(lay, m, algo, steps, warmup, xa, wa, tuning=tuning)
+        r = time_pair(lay, m, algo, steps, warmup, xa, wa, plan=tp)
         ms = r["body_ms"] * 1e-3
         row = {"workload": lay.tag(m), "m": m, "algo": algo, "tiles_per_wg": R, "k_per_wg": kit,
                "ms_per_call": r["ms_per_step"], "kernel_ms": r["body_ms"],
@@ -442,7 +441,6 @@ def main():
                 _, _, tR, tkit = tp.params()
                 tuned_blocking = (tR, tkit)
                 cases.append((tp.m, tp.algo, "tuned"))
-                tp.close()
             if lay.C >= 128:
                 # every work item split into channel pieces (partial outputs added)
                 cases += [(mm, "fused", "fused_csplit%d" % P) for P in (2, 4)]
@@ -459,10 +457,8 @@ def main():
                 elif label.startswith("fused_R"):
                     R, kit = (int(v) for v in label[len("fused_R"):].split("_K"))
                     tuning = {"tiles_per_wg": R, "k_per_wg": kit}
-                elif label == "tuned" and algo == "fused":
-                    tuning = {"tiles_per_wg": tuned_blocking[0], "k_per_wg": tuned_blocking[1]}
                 r = time_pair(lay, m_c, algo, args.steps, args.warmup, xa, wa, per_call=True,
-                              tuning=tuning)
+                              tuning=tuning, plan=tp if label == "tuned" else None)
                 wl = lay.name + "/FFT(16x16 tiles)" if algo == "fft" else lay.tag(m_c)
                 row = {"workload": wl, "algo": label, "ms_per_step": r["ms_per_step"],
                        "eff_tflops": r["direct_flops"] / (r["ms_per_step"] * 1e-3) / 1e12,

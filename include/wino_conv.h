@@ -102,17 +102,17 @@ enum {
  *                   (results do not depend on the order pieces run in, but differ
  *                   from the unsplit sum by rounding).  0 or 1: no split; at most
  *                   WINO_MAX_CHANNEL_SPLITS.
- * Automatic choice (wino_conv_plan): the largest task that fits (k at its
+ * Automatic choice (wino_conv_plan, all fields 0): the split-product kernel (fp32
+ * products as six products of bf16 terms on the bf16 matrix cores, fp32 accumulation;
+ * m = 2, 4, 5, 6) when the layer has enough tasks for it; it takes 32 tiles x 64 output
+ * channels (m = 5, 6: 32) and 16 input channels at a time.  Otherwise, and whenever a
+ * field is given, the fp32 kernel: the largest task that fits (k at its
  * maximum, R = 32 for m = 2 with C <= 64, else 16: most reuse of each
  * transformed input tile and transformed-kernel operand) as long as the layer has
  * at least one task per compute unit; otherwise the blocking with the most
- * tasks.  wino_conv_plan_tuned measures every blocking instead.
- * The blockings (2; 32, 64), (4; 16, 64), (5; 16, 32) and (6; 16, 32), chosen or
- * asked for, run on the split-product kernel (fp32 products as six products of bf16
- * terms on the bf16 matrix cores, fp32 accumulation) when the layer has enough tasks
- * for it; it takes 32 tiles x 64 output channels (m = 5, 6: 32) and 16 input channels
- * at a time.  wino_conv_describe
- * names the kernel a plan runs.  Its results are those of the fp32 kernel to fp32
+ * tasks.  wino_conv_plan_tuned measures every blocking and both kernels
+ * instead.  wino_conv_describe
+ * names the kernel a plan runs.  The split-product kernel's results are those of the fp32 kernel to fp32
  * rounding over the whole range of float: values are multiplied at a scale that keeps
  * all terms of the smallest, denormal ones included, and output tiles whose sums
  * leave the scaled range (transformed values of 2^102 and more, sums of products of

@@ -7,8 +7,8 @@
  * and stored in a wisdom file.  Here the tuned parameters are the tile size m of
  * F(m x m, 3 x 3), m in {2, 4, 5, 6} (the paper's T = m + 2), the fused kernel's
  * blocking at each m -- tiles per task R and output channels per task, every
- * blocking the kernel is built for (wino_fused_blockings) -- and, optionally,
- * the algorithm (three-stage at each m and at m = 7, or the FFT-tile algorithm
+ * blocking the fp32 kernel is built for (wino_fused_blockings), and the split-product
+ * kernel, which has one task size -- and, optionally, the algorithm (three-stage at each m and at m = 7, or the FFT-tile algorithm
  * with m = 14).
  * A tuning result is remembered per (GPU architecture, compute units, N, C, K,
  * H, W, candidate set) in a process-wide wisdom table that can be written to and
@@ -18,9 +18,9 @@
  *     <arch> <cus> <N> <C> <K> <H> <W> <candidates> <m> <algo> <R> <k> <microseconds>
  * arch is the device's architecture name (e.g. gfx950), candidates is the
  * candidate mask in hexadecimal (0x...), algo is 0 (fused), 1 (three-stage) or
- * 2 (FFT, with m = 14), R and k the fused blocking (tiles and output channels per
- * task; 0 0 for the other algorithms) and microseconds the measured time per
- * call of back-to-back calls.
+ * 2 (FFT, with m = 14), R and k the fused fp32 kernel's blocking (tiles and output
+ * channels per task; 0 0 for the split-product kernel and for the other algorithms) and
+ * microseconds the measured time per call of back-to-back calls.
  *
  * Thread safety: the wisdom table is guarded by a lock; plans are as in
  * wino_conv.h (one stream at a time).
@@ -64,8 +64,8 @@ enum {
 wino_plan *wino_conv_plan_tuned(int N, int C, int K, int H, int W, unsigned candidates,
                                 int *chosen_m, int *chosen_algo, double *call_us);
 
-/* The tile size m, algorithm and fused blocking (tiles and output channels per
- * task; 0 for the other algorithms) of a plan.  Any output pointer may be NULL.
+/* The tile size m, algorithm and fused fp32 blocking (tiles and output channels per
+ * task; 0 for the split-product kernel and for the other algorithms) of a plan.  Any output pointer may be NULL.
  * Returns WINO_EINVAL for a NULL plan. */
 int wino_conv_plan_params(const wino_plan *p, int *m, int *algo, int *tiles_per_wg, int *k_per_wg);
 

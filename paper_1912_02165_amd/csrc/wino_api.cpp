@@ -239,8 +239,8 @@ extern "C" {
 
 const char *wino_last_error(void) { return g_err.c_str(); }
 
-wino_plan *wino_conv_plan_ex(int N, int C, int K, int H, int W, int m, int algo,
-                             const wino_tuning *t) {
+static wino_plan *make_plan(int N, int C, int K, int H, int W, int m, int algo, const wino_tuning *t,
+                            wino::FusedKernel kernel) {
     Geometry g;
     if (algo != WINO_ALGO_FUSED && algo != WINO_ALGO_THREE_STAGE && algo != WINO_ALGO_FFT) {
         set_err("unknown algorithm %d", algo);
@@ -326,8 +326,9 @@ wino_plan *wino_conv_plan_ex(int N, int C, int K, int H, int W, int m, int algo,
     }
     FusedCfg cfg{0, 0, num_cus, csplit, false};
     if (algo == WINO_ALGO_FUSED) {
-        // channel pieces of every item run on the fp32 kernel only, at its own blocking
-        cfg = wino::fused_cfg_default(g, num_cus, want_R, want_kit, csplit > 1);
+        // a given blocking is the fp32 kernel's, and so are channel pieces of every item
+        if (want_R || want_kit || csplit > 1) kernel = wino::FusedKernel::kFp32;
+        cfg = wino::fused_cfg_default(g, num_cus, kernel, want_R, want_kit);
         cfg.csplit = csplit;
     } else if (algo == WINO_ALGO_THREE_STAGE) {
         cfg.split = wino::three_stage_split(g);
@@ -399,6 +400,11 @@ oom:
             total_bytes);
     wino_conv_destroy(p);
     return nullptr;
+}
+
+wino_plan *wino_conv_plan_ex(int N, int C, int K, int H, int W, int m, int algo,
+                             const wino_tuning *t) {
+    return make_plan(N, C, K, H, W, m, algo, t, wino::FusedKernel::kByRule);
 }
 
 int wino_conv_plan_params(const wino_plan *p, int *m, int *algo, int *tiles_per_wg, int *k_per_wg) {
@@ -632,3 +638,7 @@ int wino_conv_copy_intermediate(const wino_plan *p, int which, float *host_dst, 
 }
 
 }  // extern "C"
+
+wino_plan *wino::plan_split(int N, int C, int K, int H, int W, int m) {
+    return make_plan(N, C, K, H, W, m, WINO_ALGO_FUSED, nullptr, FusedKernel::kSplit);
+}

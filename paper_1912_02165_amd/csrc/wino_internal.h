@@ -6,6 +6,8 @@
 #include <cstddef>
 #include <cstdint>
 
+typedef struct wino_plan wino_plan;
+
 namespace wino {
 
 // Problem geometry and device buffers of one plan.
@@ -24,8 +26,8 @@ struct Geometry {
 // output channels per work item; the input channels of a stage are 256 / R (one
 // (tile, channel) pair per producer lane).
 struct FusedCfg {
-    int R;         // tiles per item: 16 or 32
-    int kit;       // output channels per item: 16, 32 or 64
+    int R;         // fp32 kernel: tiles per item, 16 or 32 (0: split-product kernel)
+    int kit;       // output channels per item: 16, 32 or 64 (0)
     int num_cus;   // compute units of the device (persistent grid size)
     int csplit;    // channel pieces per work item (0 or 1: whole items; also the FFT algorithm's)
     bool split;    // run by the split-product kernels (wino_split.h; also the three-stage products)
@@ -149,11 +151,19 @@ int check_device_ptr(const void *p, size_t bytes, int device, const char *name);
 int check_stream_device(hipStream_t s, int device);
 bool overlap(const void *a, size_t na, const void *b, size_t nb);
 
-// Default blocking of a layer among the built ones (restricted to tiles per item
-// want_R and output channels per item want_kit where those are nonzero).  fp32_only:
-// as if there were no split-product kernel.
-FusedCfg fused_cfg_default(const Geometry &g, int num_cus, int want_R = 0, int want_kit = 0,
-                           bool fp32_only = false);
+// Kernel of a fused plan: by the rule for the layer, the fp32 one (whose blocking may be
+// given), or the split-product one where it can serve the layer at all.
+enum class FusedKernel { kByRule, kFp32, kSplit };
+// Configuration of a layer; for the fp32 kernel the default among the built blockings
+// (restricted to tiles per item want_R and output channels per item want_kit where those
+// are nonzero).
+FusedCfg fused_cfg_default(const Geometry &g, int num_cus, FusedKernel kernel = FusedKernel::kByRule, int want_R = 0,
+                           int want_kit = 0);
+// Whether kSplit gives the split-product kernel.
+bool split_possible(const Geometry &g);
+// A plan of automatic blocking with the split-product kernel (the rule's choice where
+// that cannot serve the layer); wino_conv_plan_ex otherwise.
+wino_plan *plan_split(int N, int C, int K, int H, int W, int m);
 
 // One line naming the three-stage kernels.
 void describe_three_stage(const Geometry &g, bool split, char *buf, size_t len);

@@ -652,9 +652,7 @@ bool fused_blocking_built(int m, int R, int kit) {
 template <int M>
 static bool split_enough(const Geometry &g, int num_cus) {
     using S = SplitShape<M>;
-    if (g.C <= S::CC) return false;
     const SplitInfo si = split_kernel_info<M>(g, num_cus);
-    if ((unsigned long long)S::KB * si.stages * S::T2 * kSplitOperandBytes >> 32) return false;
     if (M == 5 && 4 * g.K < 3 * si.n_kgroups * S::KIT) return false;
     const double items = (double)si.n_items * g.K / (si.n_kgroups * S::KIT);
     if (16.0 * items >= (M == 2 ? 3.0 : 5.0) * num_cus) return true;
@@ -662,14 +660,24 @@ static bool split_enough(const Geometry &g, int num_cus) {
     return (si.stages >= 6 && 4.0 * items > num_cus) || (si.stages >= 16 && 8.0 * items >= num_cus);
 }
 static bool split_fits(const Geometry &g, int num_cus) {
+    if (!split_possible(g)) return false;
 #define WINO_SPLIT_ENOUGH(m_) \
     if (g.m == m_) return split_enough<m_>(g, num_cus);
     WINO_SPLIT_M(WINO_SPLIT_ENOUGH)
 #undef WINO_SPLIT_ENOUGH
     return false;
 }
-// The blocking whose requests it serves: the largest task of the fp32 kernel.
-static bool split_blocking(int m, int R, int kit) { return R == (m == 2 ? 32 : 16) && kit == (m <= 4 ? 64 : 32); }
+bool split_possible(const Geometry &g) {
+#define WINO_SPLIT_POSSIBLE(m_)                                                                                \
+    if (g.m == m_) {                                                                                           \
+        using S = SplitShape<m_>;                                                                              \
+        const unsigned long long stages = (g.C + S::CC - 1) / S::CC;                                           \
+        return stages > 1 && (S::KB * stages * S::T2 * kSplitOperandBytes >> 32) == 0;                         \
+    }
+    WINO_SPLIT_M(WINO_SPLIT_POSSIBLE)
+#undef WINO_SPLIT_POSSIBLE
+    return false;
+}
 
 // Default blocking of a layer, from the capacity bounds of Sec. 4.1 and the
 // number of work items.
@@ -691,16 +699,16 @@ static bool split_blocking(int m, int R, int kit) { return R == (m == 2 ? 32 : 1
 // Measured on every layer (steady state, one MI355X): splitting a task's output
 // channels among its consumer waves costs more than the transform reuse it gives
 // up whenever the larger tasks already fill the compute units.
-FusedCfg fused_cfg_default(const Geometry &g, int num_cus, int want_R, int want_kit, bool fp32_only) {
+FusedCfg fused_cfg_default(const Geometry &g, int num_cus, FusedKernel kernel, int want_R, int want_kit) {
+    if (kernel == FusedKernel::kSplit ? split_possible(g) : kernel == FusedKernel::kByRule && split_fits(g, num_cus))
+        return FusedCfg{0, 0, num_cus, 0, true};
     FusedCfg best{};
     int best_items = -1;
     bool best_fills = false;
     const int pref_R = (g.m == 2 && g.C <= 64) ? 32 : 16;
-    const bool split = !fp32_only && split_fits(g, num_cus);
     for (const FusedBlocking &b : kFusedBlockings) {
         if (b.m != g.m || (want_R && b.R != want_R) || (want_kit && b.kit != want_kit)) continue;
-        const FusedCfg c{b.R, b.kit, num_cus, 0, split && split_blocking(b.m, b.R, b.kit)};
-        if (c.split) return c;
+        const FusedCfg c{b.R, b.kit, num_cus, 0, false};
         const int items = fused_split_info(g, c).n_items;
         const bool fills = items >= num_cus;
         bool take;
@@ -765,7 +773,6 @@ void describe_fused(const Geometry &g, const FusedCfg &cfg, char *buf, size_t le
 
 hipError_t launch_fused(const Geometry &g, const FusedCfg &cfg, const float *x, const float *wt,
                         float *y, const SplitBuffers &sb, hipStream_t s) {
-    if (!fused_blocking_built(g.m, cfg.R, cfg.kit)) return hipErrorInvalidValue;
     if (cfg.split) {
 #define WINO_LAUNCH_SPLIT(m_) \
     if (g.m == m_) return launch_split_t<m_>(g, x, wt, y, cfg.num_cus, sb, s);
@@ -773,6 +780,7 @@ hipError_t launch_fused(const Geometry &g, const FusedCfg &cfg, const float *x, 
 #undef WINO_LAUNCH_SPLIT
         return hipErrorInvalidValue;
     }
+    if (!fused_blocking_built(g.m, cfg.R, cfg.kit)) return hipErrorInvalidValue;
     const uintptr_t ya = reinterpret_cast<uintptr_t>(y);
     // rows of whole tiles stored as vectors: 16-byte aligned for m = 4, 8-byte for m =
     // 2, 6; m = 5 uses buffer stores that need only 4-byte alignment

@@ -100,7 +100,7 @@ extern "C" int wino_conv_run_noalloc(int N, int C, int K, int H, int W, int m, c
     const size_t cnt_bytes = si.n_tail > 0 ? (size_t)si.n_tail * sizeof(unsigned) : 0;
     const size_t part_bytes = si.n_tail > 0 ? (size_t)si.n_tail * si.maxc * si.part_floats * sizeof(float) : 0;
     // what the limit counts
-    const wino::SplitInfo ci = wino::fused_split_info(g, wino::fused_cfg_default(g, ds.cus, 0, 0, true));
+    const wino::SplitInfo ci = wino::fused_split_info(g, wino::fused_cfg_default(g, ds.cus, wino::FusedKernel::kFp32));
     const size_t counted = kAlign + align_up(ci.counted_units > 0 ? (size_t)ci.n_tail * sizeof(unsigned) : 0) +
                            align_up((size_t)ci.counted_units * ci.part_floats * sizeof(float)) + align_up(wt_bytes);
     // layout: [status word | split counters | partial outputs | transformed kernels]

@@ -20,7 +20,7 @@ namespace {
 using Key = std::tuple<std::string, int, int, int, int, int, int, unsigned>;  // arch, cus, N, C, K, H, W, mask
 struct Choice {
     int m, algo;
-    int R, kit;  // fused blocking (0 for the other algorithms)
+    int R, kit;  // fused blocking (0: split-product kernel, or another algorithm)
     double us;
 };
 
@@ -44,11 +44,13 @@ bool choice_ok(unsigned c, int m, int algo, int R, int kit) {
     if (m != 2 && m != 4 && m != 5 && m != 6 && m != 7) return false;
     if (!(c & (1u << m))) return false;
     if (algo == WINO_ALGO_THREE_STAGE) return (c & WINO_TUNE_THREE_STAGE) != 0 && R == 0 && kit == 0;
-    return algo == WINO_ALGO_FUSED && wino::fused_blocking_built(m, R, kit);
+    if (algo != WINO_ALGO_FUSED || m == 7) return false;
+    return (R == 0 && kit == 0) || wino::fused_blocking_built(m, R, kit);
 }
 
-// The plan of a choice: the fused blocking as an override.
+// The plan of a choice: the fused blocking as an override (which is the fp32 kernel's).
 wino_plan *plan_of(int N, int C, int K, int H, int W, const Choice &c) {
+    if (c.algo == WINO_ALGO_FUSED && c.R == 0) return wino::plan_split(N, C, K, H, W, c.m);
     wino_tuning t{};
     t.tiles_per_wg = c.R;
     t.k_per_wg = c.kit;
@@ -174,13 +176,19 @@ wino_plan *wino_conv_plan_tuned(int N, int C, int K, int H, int W, unsigned cand
         if (it != g_table.end()) best = it->second;
     }
     if (best.m == 0) {
-        // candidates: per tile size every built fused blocking, the three-stage
-        // algorithm if asked for, and the FFT-tile algorithm if asked for
+        // candidates: per tile size every built fused blocking (on the fp32 kernel), the
+        // split-product kernel, the three-stage algorithm if asked for, and the FFT-tile
+        // algorithm if asked for
         std::vector<Choice> cands;
         for (int m : {2, 4, 5, 6, 7}) {
             if (!(candidates & (1u << m))) continue;
             for (const wino::FusedBlocking &b : wino::kFusedBlockings)
                 if (b.m == m) cands.push_back(Choice{m, WINO_ALGO_FUSED, b.R, b.kit, 0.0});
+            wino::Geometry g;
+            if (m != 7) {
+                if (wino::make_geometry(N, C, K, H, W, m, WINO_ALGO_FUSED, &g) != WINO_OK) return nullptr;
+                if (wino::split_possible(g)) cands.push_back(Choice{m, WINO_ALGO_FUSED, 0, 0, 0.0});
+            }
             if (candidates & WINO_TUNE_THREE_STAGE) cands.push_back(Choice{m, WINO_ALGO_THREE_STAGE, 0, 0, 0.0});
         }
         if (candidates & WINO_TUNE_FFT) cands.push_back(Choice{14, WINO_ALGO_FFT, 0, 0, 0.0});

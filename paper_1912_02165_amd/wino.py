@@ -219,7 +219,8 @@ def wino_conv_plan_tuned(N, C, K, H, W, candidates=WINO_TUNE_ALL_M):
 
 
 def wino_conv_plan_params(plan):
-    """(m, algo, tiles_per_wg, k_per_wg) of a plan (the last two 0 unless fused)."""
+    """(m, algo, tiles_per_wg, k_per_wg) of a plan (the last two 0 unless it runs the fused fp32
+    kernel)."""
     m, algo, R, kit = ctypes.c_int(), ctypes.c_int(), ctypes.c_int(), ctypes.c_int()
     _check(lib().wino_conv_plan_params(plan, ctypes.byref(m), ctypes.byref(algo), ctypes.byref(R),
                                        ctypes.byref(kit)))

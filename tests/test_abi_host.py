@@ -314,3 +314,21 @@ def test_noalloc_checks_before_any_hip_call(lib):
     assert "scratch" in wc.wino_last_error()
     with open(os.path.join(ROOT, "include", "wino_conv.h")) as f:
         assert re.search(r"#define WINO_NOALLOC_SCRATCH_BYTES \(16u << 20\)", f.read())
+
+
+def test_wisdom_split_product_kernel(lib, tmp_path):
+    """A fused entry of blocking 0 0 is the split-product kernel's: it round-trips, and is
+    malformed for a tile size without that kernel."""
+    wc.wino_wisdom_clear()
+    line = "gfx950 256 32 64 64 224 224 0x54 4 0 0 0 317.000\n"
+    src, out = tmp_path / "in.txt", tmp_path / "out.txt"
+    src.write_text(line)
+    wc.wino_wisdom_load(str(src))
+    assert wc.wino_wisdom_lookup("gfx950", 256, 32, 64, 64, 224, 224, 0x54) == (4, 0, 0, 0)
+    wc.wino_wisdom_save(str(out))
+    assert out.read_text().splitlines()[-1] + "\n" == line
+    for bad in ("0x1d4 7 0 0 0 1.0", "0x54 4 0 16 0 1.0", "0x54 4 0 0 64 1.0"):
+        src.write_text("gfx950 256 32 64 64 224 224 " + bad + "\n")
+        with pytest.raises(wc.WinoError, match="malformed"):
+            wc.wino_wisdom_load(str(src))
+    wc.wino_wisdom_clear()

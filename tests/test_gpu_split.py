@@ -413,3 +413,57 @@ def test_three_stage_padding_frequencies_zero():
         M = _unfold(p.intermediate(wc.WINO_BUF_PRODUCT), "M")
     assert np.isnan(M[:49]).any() or np.isinf(M[:49]).any()
     assert not M[49:].any()
+
+
+@pytest.mark.parametrize("shape,m", [((20, 64, 64, 46, 46), 2), ((20, 64, 64, 46, 46), 4), ((16, 128, 128, 28, 28), 5),
+                                     ((32, 128, 128, 28, 28), 6)])
+def test_given_blocking_is_the_fp32_kernels(shape, m):
+    """Every blocking asked for runs on the fp32 kernel, at that blocking, also on layers
+    that run on the split-product kernel otherwise; the plan's parameters tell them apart."""
+    x, w, xd, wd = _device(shape, 17)
+    N, C, K, H, W = shape
+    ref = direct_conv(x, w)
+    with wc.Plan(*shape, m) as p:
+        assert "split products" in p.describe() and p.params() == (m, 0, 0, 0)
+    for bm, R, kit in wc.wino_fused_blockings():
+        if bm != m:
+            continue
+        y = torch.full((N, K, H, W), float("nan"), device="cuda")
+        with wc.Plan(*shape, m, "fused", {"tiles_per_wg": R, "k_per_wg": kit}) as p:
+            d = p.describe()
+            assert "split products" not in d and f"R={R} " in d and f"Kit={kit} " in d, d
+            assert p.params() == (m, 0, R, kit)
+            p.run(xd, wd, y)
+            p.status()
+        assert_close(y.cpu().numpy(), ref, m, f"F({m}) {R} x {kit}")
+
+
+def test_tuned_plan_has_both_kernels(tmp_path):
+    """The tuner times the split-product kernel beside every fp32 blocking: where the rule
+    takes it by a wide margin so does the tuner, a wisdom entry keeps the choice, an entry
+    with a blocking gives the fp32 kernel, and one of the split-product kernel gives it
+    also where the rule does not."""
+    shape = (64, 128, 128, 28, 28)
+    prop = torch.cuda.get_device_properties(0)
+    key = "%s %d " % (prop.gcnArchName.split(":")[0], prop.multi_processor_count)
+    wc.wino_wisdom_clear()
+    with wc.Plan.tuned(*shape, wc.WINO_TUNE_M4) as p:
+        assert "split products" in p.describe() and p.params() == (4, 0, 0, 0)
+    f = tmp_path / "w.txt"
+    wc.wino_wisdom_save(str(f))
+    assert " 0x10 4 0 0 0 " in f.read_text()
+    few = (1, 64, 64, 56, 56)
+    f.write_text(key + "64 128 128 28 28 0x10 4 0 16 64 50.0\n" + key + "1 64 64 56 56 0x10 4 0 0 0 50.0\n")
+    wc.wino_wisdom_load(str(f))
+    with wc.Plan.tuned(*shape, wc.WINO_TUNE_M4) as p:
+        assert "split products" not in p.describe() and p.params() == (4, 0, 16, 64)
+    with wc.Plan(*few, 4) as p:
+        assert "split products" not in p.describe()
+    x, w, xd, wd = _device(few, 18)
+    y = torch.full((1, 64, 56, 56), float("nan"), device="cuda")
+    with wc.Plan.tuned(*few, wc.WINO_TUNE_M4) as p:
+        assert "split products" in p.describe()
+        p.run(xd, wd, y)
+        p.status()
+    assert_close(y.cpu().numpy(), direct_conv(x, w), 4, "split-product kernel by wisdom")
+    wc.wino_wisdom_clear()
