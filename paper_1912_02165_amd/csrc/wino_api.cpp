@@ -324,7 +324,7 @@ static wino_plan *make_plan(int N, int C, int K, int H, int W, int m, int algo, 
         }
         num_cus = cus;
     }
-    FusedCfg cfg{0, 0, num_cus, csplit, false};
+    FusedCfg cfg{0, 0, num_cus, csplit, false, false};
     if (algo == WINO_ALGO_FUSED) {
         // a given blocking is the fp32 kernel's, and so are channel pieces of every item
         if (want_R || want_kit || csplit > 1) kernel = wino::FusedKernel::kFp32;

@@ -31,6 +31,7 @@ struct FusedCfg {
     int num_cus;   // compute units of the device (persistent grid size)
     int csplit;    // channel pieces per work item (0 or 1: whole items; also the FFT algorithm's)
     bool split;    // run by the split-product kernels (wino_split.h; also the three-stage products)
+    bool own;      // their P waves add a stage's products on their own (SplitShape)
 };
 
 // Tile sizes the split-product fused kernel is built for: X(m).

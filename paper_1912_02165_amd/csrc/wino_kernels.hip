@@ -16,7 +16,7 @@ namespace wino {
 WINO_FUSED_BLOCKINGS(WINO_EXTERN_WS)
 #undef WINO_EXTERN_WS
 #define WINO_EXTERN_SPLIT(m) \
-    extern template hipError_t launch_split_t<m>(const Geometry &, const float *, const float *, float *, int, \
+    extern template hipError_t launch_split_t<m>(const Geometry &, const float *, const float *, float *, int, bool, \
                                                  const SplitBuffers &, hipStream_t);
 WINO_SPLIT_M(WINO_EXTERN_SPLIT)
 #undef WINO_EXTERN_SPLIT
@@ -678,6 +678,29 @@ bool split_possible(const Geometry &g) {
 #undef WINO_SPLIT_POSSIBLE
     return false;
 }
+// The split-product kernel's configuration (R = 0), or of the fp32 kernel (R > 0).
+// Precision: where the fp32 kernel would run at a blocking that adds two halves of the
+// channels (layers too small for its larger tasks), its error is 4 to 12% below that of this
+// kernel's single sums from three stages on.  There F(2) and F(4) add stages on their own
+// (SplitShape; error 0.72-0.85 of the fp32 kernel's; F(2) 4 images of 56 x 56, 64 channels
+// 12.4 -> 13.0 us, fp32 kernel 14.7; F(4) 20 of 46 x 46 22.9 -> 24.5, fp32 34.1), F(5) and F(6)
+// cut their items into two and more pieces (0.72-0.86; F(6) 34.1 -> 33.5, fp32 40.9; F(5)
+// 29.8 -> 29.9, fp32 31.8), and F(5) of three stages, which that makes slower than the fp32
+// kernel (29.3 against 27.2), is left to it.
+static bool split_cfg(const Geometry &g, int num_cus, FusedKernel kernel, FusedCfg *cfg) {
+    if (kernel == FusedKernel::kFp32 || !split_possible(g)) return false;
+    if (kernel == FusedKernel::kByRule && !split_fits(g, num_cus)) return false;
+    *cfg = FusedCfg{0, 0, num_cus, 0, true, false};
+    const SplitInfo si = fused_split_info(g, *cfg);
+    if (si.stages < 3 || si.n_tail > 0) return true;
+    const FusedCfg f = fused_cfg_default(g, num_cus, FusedKernel::kFp32);
+    bool halves = false;
+    for (const FusedBlocking &b : kFusedBlockings)
+        if (b.m == g.m && b.R == f.R && b.kit == f.kit) halves = b.csp == 2;
+    if (halves && g.m > 4) return false;
+    cfg->own = halves;
+    return true;
+}
 
 // Default blocking of a layer, from the capacity bounds of Sec. 4.1 and the
 // number of work items.
@@ -700,15 +723,15 @@ bool split_possible(const Geometry &g) {
 // channels among its consumer waves costs more than the transform reuse it gives
 // up whenever the larger tasks already fill the compute units.
 FusedCfg fused_cfg_default(const Geometry &g, int num_cus, FusedKernel kernel, int want_R, int want_kit) {
-    if (kernel == FusedKernel::kSplit ? split_possible(g) : kernel == FusedKernel::kByRule && split_fits(g, num_cus))
-        return FusedCfg{0, 0, num_cus, 0, true};
     FusedCfg best{};
+    if (split_cfg(g, num_cus, kernel, &best)) return best;
+    best = FusedCfg{};
     int best_items = -1;
     bool best_fills = false;
     const int pref_R = (g.m == 2 && g.C <= 64) ? 32 : 16;
     for (const FusedBlocking &b : kFusedBlockings) {
         if (b.m != g.m || (want_R && b.R != want_R) || (want_kit && b.kit != want_kit)) continue;
-        const FusedCfg c{b.R, b.kit, num_cus, 0, false};
+        const FusedCfg c{b.R, b.kit, num_cus, 0, false, false};
         const int items = fused_split_info(g, c).n_items;
         const bool fills = items >= num_cus;
         bool take;
@@ -751,9 +774,9 @@ void describe_fused(const Geometry &g, const FusedCfg &cfg, char *buf, size_t le
         snprintf(buf, len,
                  "fused_ws_kernel<M=%d,split products> R=%d tiles x Kit=%d output channels per item, 16 input channels per "
                  "stage, %d items (%d tile groups x %d channel groups), %d stages per item, grid %d, split items %d "
-                 "x %d pieces",
+                 "x %d pieces%s",
                  g.m, 32, g.m <= 4 ? 64 : 32, si.n_items, si.n_items / si.n_kgroups, si.n_kgroups,
-                 si.stages, si.grid, si.n_tail, si.maxc);
+                 si.stages, si.grid, si.n_tail, si.maxc, cfg.own ? ", stages added on their own" : "");
         return;
     }
     int tb = 0, fs = 0, csp = 0;
@@ -775,7 +798,7 @@ hipError_t launch_fused(const Geometry &g, const FusedCfg &cfg, const float *x, 
                         float *y, const SplitBuffers &sb, hipStream_t s) {
     if (cfg.split) {
 #define WINO_LAUNCH_SPLIT(m_) \
-    if (g.m == m_) return launch_split_t<m_>(g, x, wt, y, cfg.num_cus, sb, s);
+    if (g.m == m_) return launch_split_t<m_>(g, x, wt, y, cfg.num_cus, cfg.own, sb, s);
         WINO_SPLIT_M(WINO_LAUNCH_SPLIT)
 #undef WINO_LAUNCH_SPLIT
         return hipErrorInvalidValue;

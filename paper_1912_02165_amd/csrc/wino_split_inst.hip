@@ -8,7 +8,7 @@
 
 namespace wino {
 
-template hipError_t launch_split_t<WS_M>(const Geometry &, const float *, const float *, float *, int,
+template hipError_t launch_split_t<WS_M>(const Geometry &, const float *, const float *, float *, int, bool,
                                          const SplitBuffers &, hipStream_t);
 
 }  // namespace wino

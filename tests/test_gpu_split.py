@@ -467,3 +467,33 @@ def test_tuned_plan_has_both_kernels(tmp_path):
         p.status()
     assert_close(y.cpu().numpy(), direct_conv(x, w), 4, "split-product kernel by wisdom")
     wc.wino_wisdom_clear()
+
+
+# layers where the fp32 kernel runs at a blocking that adds two halves of the channels: at
+# both ends of the rule's range, ragged, in three stages and more, both item orders
+HALVES = [((4, 64, 64, 56, 56), 2), ((4, 37, 45, 57, 61), 2), ((4, 112, 64, 56, 56), 2), ((20, 80, 64, 46, 46), 4),
+          ((1, 64, 64, 224, 224), 4), ((24, 33, 60, 46, 45), 4), ((20, 64, 64, 46, 46), 5), ((20, 80, 64, 46, 46), 5),
+          ((20, 33, 64, 46, 46), 5), ((20, 64, 64, 46, 46), 6), ((20, 33, 64, 46, 46), 6), ((1, 48, 64, 224, 224), 6)]
+
+
+@pytest.mark.parametrize("case", HALVES, ids=_id)
+def test_error_no_larger_than_two_halves(case):
+    """Against fp64, a layer's error is no larger than at the blocking the fp32 kernel would
+    take by itself: there one that adds two halves of the channels.  (Both errors are
+    norms over more than 500,000 outputs, so chance moves them by well under 1%.)"""
+    (N, C, K, H, W), m = case
+    x, w, xd, wd = _device(case[0], 400 + m + C)
+    ref = direct_conv(x, w)
+    rel = []
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    tiles = -(-(N * -(-H // m) * -(-W // m)) // 16)
+    fp32 = {2: (16, 32), 4: (16, 32), 5: (16, 16), 6: (16, 16)}[m]
+    assert tiles * -(-K // (64 if m <= 4 else 32)) < cus  # the larger blockings do not fill the device
+    for tuning in (None, {"tiles_per_wg": fp32[0], "k_per_wg": fp32[1]}):
+        y = torch.full((N, K, H, W), float("nan"), device="cuda")
+        with wc.Plan(N, C, K, H, W, m, "fused", tuning) as p:
+            p.run(xd, wd, y)
+            p.status()
+        rel.append(errors(y.cpu().numpy(), ref)[0])
+    print(f"{_id(case)} {rel[0]:.3e} two halves {rel[1]:.3e} ratio {rel[0] / rel[1]:.3f}")
+    assert rel[0] <= 1.01 * rel[1]
