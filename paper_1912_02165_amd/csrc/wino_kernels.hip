@@ -480,8 +480,8 @@ __global__ void __launch_bounds__(256, 3) frequency_gemm_split_kernel(const floa
         return Mout + (((((long long)f4 * TB + tb) * g.Kb_alloc + kb16) * 4 + v % 4) * 64 + l16) * 4 + 2 * fp;
     };
     // a frequency past T^2 (the wave's second one only) is zero, whatever the kernels repeated for it hold
-    const int f0 = 4 * f4 + 2 * fp, nf = T2 - f0 < 2 ? (T2 - f0 < 0 ? 0 : T2 - f0) : 2;
-    float sum = 0.0f;  // of the results: not finite if one of them is not
+    const int f0 = 4 * f4 + 2 * fp, nf = T2 % 4 == 0 || T2 - f0 >= 2 ? 2 : T2 - f0 < 0 ? 0 : T2 - f0;
+    float sum[4] = {};  // of the results: not finite if one of them is not
 #pragma unroll
     for (int k = 0; k < 2; ++k)
 #pragma unroll
@@ -490,13 +490,13 @@ __global__ void __launch_bounds__(256, 3) frequency_gemm_split_kernel(const floa
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 r[i] = i < nf ? acc[i][k][v] * kSplitUnscale : 0.0f;
-                sum += acc[i][k][v];
+                sum[v % 4] += acc[i][k][v];
             }
             *reinterpret_cast<floatx2 *>(out(k, v)) = r;
         }
     // Sums beyond the scaled range (or of infinities) again, as fp32 products: the lane's
     // element of each of its tiles' frequencies straight from U and the kernels.
-    if (__builtin_amdgcn_ballot_w64(!finite(sum)) == 0) return;
+    if (__builtin_amdgcn_ballot_w64(!finite((sum[0] + sum[1]) + (sum[2] + sum[3]))) == 0) return;
     unsigned again[2] = {0u, 0u};  // bit 16 k + v
 #pragma unroll
     for (int i = 0; i < 2; ++i)
