@@ -69,10 +69,11 @@ __device__ void raw_buffer_store_f32x4(floatx4 v, int32x4 rsrc, unsigned voffset
 // instruction must not overwrite them.  The compiler sees to that only where the scalar
 // offset is a constant; with one in a register the stored value was the overwriting one now
 // and then.  The data stay in use past one idle cycle.
+__device__ __forceinline__ void hold_store_data(floatx4 v) { asm volatile("s_nop 0" ::"v"(v)); }
 __device__ __forceinline__ void buffer_store_f32x4(floatx4 v, int32x4 rsrc, unsigned voffset, unsigned soffset,
                                                    int aux) {
     raw_buffer_store_f32x4(v, rsrc, voffset, soffset, aux);
-    asm volatile("s_nop 0" ::"v"(v));
+    hold_store_data(v);
 }
 __device__ void buffer_store_f32x2(floatx2 v, int32x4 rsrc, unsigned voffset, unsigned soffset, int aux)
     __asm("llvm.amdgcn.raw.buffer.store.v2f32");
@@ -335,19 +336,25 @@ struct RowTile {
 
 // Store one row of m output floats through a buffer resource over y: the row's
 // first element at byte offset voff (per lane) + so (uniform).  STREAM: streaming
-// (non-temporal) cache policy.
-template <int M, bool STREAM>
+// (non-temporal) cache policy.  HOLD: hold_store_data after the row; without, the caller's.
+template <int M, bool STREAM, bool HOLD = true>
 __device__ __forceinline__ void store_row_buf(int32x4 yrs, unsigned voff, unsigned so, const float *r) {
     constexpr int kAux = STREAM ? kStream : 0;
     if constexpr (M == 4) {
-        buffer_store_f32x4(floatx4{r[0], r[1], r[2], r[3]}, yrs, voff, so, kAux);
+        const floatx4 v{r[0], r[1], r[2], r[3]};
+        raw_buffer_store_f32x4(v, yrs, voff, so, kAux);
+        if constexpr (HOLD) hold_store_data(v);
     } else if constexpr (M == 5) {  // 4-byte aligned vector store + one float
-        buffer_store_f32x4(floatx4{r[0], r[1], r[2], r[3]}, yrs, voff, so, kAux);
+        const floatx4 v{r[0], r[1], r[2], r[3]};
+        raw_buffer_store_f32x4(v, yrs, voff, so, kAux);
         buffer_store_f32(r[4], yrs, voff + 16u, so, kAux);
+        if constexpr (HOLD) hold_store_data(v);
     } else if constexpr (M == 7) {  // 4-byte aligned: 4 + 2 + 1 floats
-        buffer_store_f32x4(floatx4{r[0], r[1], r[2], r[3]}, yrs, voff, so, kAux);
+        const floatx4 v{r[0], r[1], r[2], r[3]};
+        raw_buffer_store_f32x4(v, yrs, voff, so, kAux);
         buffer_store_f32x2(floatx2{r[4], r[5]}, yrs, voff + 16u, so, kAux);
         buffer_store_f32(r[6], yrs, voff + 24u, so, kAux);
+        if constexpr (HOLD) hold_store_data(v);
     } else {
 #pragma unroll
         for (int jj = 0; jj < M; jj += 2) buffer_store_f32x2(floatx2{r[jj], r[jj + 1]}, yrs, voff + 4u * jj, so, kAux);
@@ -356,12 +363,19 @@ __device__ __forceinline__ void store_row_buf(int32x4 yrs, unsigned voff, unsign
 
 // Store one m x m output tile that lies wholly inside the image: its first element
 // at byte offset voff (per lane) + soff (uniform), rows rowb bytes apart (uniform),
-// so the per-row and per-channel steps are scalar adds.
+// so the per-row and per-channel steps are scalar adds.  The stores follow each other and the
+// data are held after the last: with an idle cycle between the stores of a row, the parts of a
+// line reached memory on their own when y outgrew the caches (F(5), 512 images of 40 x 40,
+// C = 32, K = 64 192 us for 128; 1 of 2040 x 2040, C = 17, K = 128 1640 for 1290).
 template <int M, bool STREAM>
 __device__ __forceinline__ void store_rows_buf(int32x4 yrs, unsigned voff, unsigned soff, unsigned rowb,
                                                const float *yy) {
 #pragma unroll
-    for (int i = 0; i < M; ++i) store_row_buf<M, STREAM>(yrs, voff, soff + (unsigned)i * rowb, yy + i * M);
+    for (int i = 0; i < M; ++i) store_row_buf<M, STREAM, false>(yrs, voff, soff + (unsigned)i * rowb, yy + i * M);
+    if constexpr (M == 4 || M == 5 || M == 7) {
+#pragma unroll
+        for (int i = 0; i < M; ++i) hold_store_data(floatx4{yy[i * M], yy[i * M + 1], yy[i * M + 2], yy[i * M + 3]});
+    }
 }
 
 // Store one m x m output tile of plane yp (clipped to H x W).  vec: rows may be
