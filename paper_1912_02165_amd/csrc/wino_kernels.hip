@@ -64,14 +64,16 @@ __global__ void __launch_bounds__(256) weight_transform_kernel(const float *__re
 // Kernel transform into split-product operands (launch_weight_transform_split): a
 // workgroup transforms 32 output x 16 input channels, one kernel per thread (input
 // channel fastest, so that w is read in runs of 16 kernels), splits each value into
-// its three bf16 terms and passes FCH frequencies at a time through LDS, from which
-// whole operands are stored as 16-byte vectors.  blockIdx.y picks the FCH
-// frequencies a workgroup keeps (the transform of the others is dropped by the
-// compiler), which gives small layers enough workgroups.
-constexpr int kSplitFch = 16;
-template <int M, int PART>
+// its three bf16 terms and passes FCH frequencies through LDS, from which whole operands
+// are stored as 16-byte vectors.  blockIdx.y picks the FCH frequencies a workgroup keeps
+// (the transform of the others is dropped by the compiler).  Bound: latency; FCH = 16, but 8
+// up to 128 workgroups of 16 and 4 up to 64, so that more compute units have one (whole
+// calls with kernels given, us: 4 images of 57 x 61, C = 37, K = 45, F(2) 8 workgroups 15.8 ->
+// 14.9 at 4; 64 of 28 x 28, 128 channels, F(4) 96 workgroups 45.5 -> 45.0 at 8, F(6) 128 68.6
+// -> 68.1, three-stage C = 64, K = 256, F(7) 192 25.4 -> 25.7).
+template <int M, int FCH, int PART>
 __device__ __forceinline__ void weight_split_part(const float *gk, unsigned short *st, uintx4 *dst, int tid) {
-    constexpr int T2 = (M + 2) * (M + 2), F0 = PART * kSplitFch, FN = T2 - F0 < kSplitFch ? T2 - F0 : kSplitFch;
+    constexpr int T2 = (M + 2) * (M + 2), F0 = PART * FCH, FN = T2 - F0 < FCH ? T2 - F0 : FCH;
     float t[T2];
     kernel_tile_transform<M>(gk, t);
     // lane (c % 16) / 8 * 32 + k % 32, element c % 8 of each of the three terms
@@ -94,20 +96,20 @@ __device__ __forceinline__ void weight_split_part(const float *gk, unsigned shor
     for (int i = tid; i < FN * 192; i += 512) dst[F0 * 192 + i] = reinterpret_cast<const uintx4 *>(st)[i];
 }
 
-template <int M, int PART = 0>
+template <int M, int FCH, int PART = 0>
 __device__ __forceinline__ void weight_split_pick(int part, const float *gk, unsigned short *st, uintx4 *dst, int tid) {
-    if constexpr (PART * kSplitFch < (M + 2) * (M + 2)) {
-        if (part == PART) weight_split_part<M, PART>(gk, st, dst, tid);
-        else weight_split_pick<M, PART + 1>(part, gk, st, dst, tid);
+    if constexpr (PART * FCH < (M + 2) * (M + 2)) {
+        if (part == PART) weight_split_part<M, FCH, PART>(gk, st, dst, tid);
+        else weight_split_pick<M, FCH, PART + 1>(part, gk, st, dst, tid);
     }
 }
 
-template <int M>
+template <int M, int FCH>
 __global__ void __launch_bounds__(512) weight_transform_split_kernel(const float *__restrict__ w,
                                                                      uintx4 *__restrict__ wt, Geometry g,
                                                                      unsigned *zero, int nzero) {
     constexpr int T2 = (M + 2) * (M + 2);
-    __shared__ __align__(16) unsigned short st[kSplitFch * 1536];
+    __shared__ __align__(16) unsigned short st[FCH * 1536];
     const int tid = threadIdx.x;
     if (blockIdx.x == 0 && blockIdx.y == 0)
         for (int i = tid; i < nzero; i += blockDim.x) zero[i] = 0u;
@@ -119,7 +121,7 @@ __global__ void __launch_bounds__(512) weight_transform_split_kernel(const float
     float gk[9];
 #pragma unroll
     for (int i = 0; i < 9; ++i) gk[i] = ok ? src[i] : 0.0f;
-    weight_split_pick<M>(blockIdx.y, gk, st, wt + (size_t)blockIdx.x * T2 * 192, tid);
+    weight_split_pick<M, FCH>(blockIdx.y, gk, st, wt + (size_t)blockIdx.x * T2 * 192, tid);
 }
 
 // ---------------------------------------------------------------------------
@@ -598,9 +600,18 @@ hipError_t launch_weight_transform(const Geometry &g, const float *w, float *wt,
 
 hipError_t launch_weight_transform_split(const Geometry &g, const float *w, float *wt, hipStream_t s,
                                          unsigned *zero, int nzero) {
-    dim3 block(512), grid((unsigned)(g.Kb_alloc / 2 * ((g.C + 15) / 16)), (unsigned)((g.T2 + kSplitFch - 1) / kSplitFch));
-    WINO_DISPATCH_M(g.m, hipLaunchKernelGGL(weight_transform_split_kernel<MM>, grid, block, 0, s, w,
-                                            reinterpret_cast<uintx4 *>(wt), g, zero, nzero));
+    const unsigned nx = (unsigned)(g.Kb_alloc / 2 * ((g.C + 15) / 16));
+    auto go = [&](auto kern, int fch) {
+        hipLaunchKernelGGL(kern, dim3(nx, (unsigned)((g.T2 + fch - 1) / fch)), dim3(512), 0, s, w,
+                           reinterpret_cast<uintx4 *>(wt), g, zero, nzero);
+    };
+    if (nx * (unsigned)((g.T2 + 15) / 16) <= 64u) {
+        WINO_DISPATCH_M(g.m, go(weight_transform_split_kernel<MM, 4>, 4));
+    } else if (nx * (unsigned)((g.T2 + 15) / 16) <= 128u) {
+        WINO_DISPATCH_M(g.m, go(weight_transform_split_kernel<MM, 8>, 8));
+    } else {
+        WINO_DISPATCH_M(g.m, go(weight_transform_split_kernel<MM, 16>, 16));
+    }
     return hipGetLastError();
 }
 

@@ -279,7 +279,7 @@ def test_three_stage_few_tiles_large_kernels():
 # (shape, m): one image, output channels of a task missing (the epilogue's rounds of 8
 # channels past K begin past the end of y), and images lower than a tile (so do its rows)
 FEW_CHANNELS = [((1, 32, 40, 256, 257), 4), ((1, 32, 40, 250, 251), 2), ((1, 32, 24, 350, 351), 5), ((1, 32, 20, 400, 399), 6),
-                ((1, 17, 57, 1, 16390), 4), ((1, 17, 57, 1, 8190), 2), ((1, 17, 25, 1, 20003), 5), ((1, 17, 25, 1, 24003), 6),
+                ((1, 17, 57, 1, 16390), 4), ((1, 17, 57, 1, 8290), 2), ((1, 17, 25, 1, 20003), 5), ((1, 17, 25, 1, 24003), 6),
                 ((1, 17, 57, 2, 16390), 4), ((1, 17, 25, 2, 24003), 6)]
 
 
@@ -497,3 +497,24 @@ def test_error_no_larger_than_two_halves(case):
         rel.append(errors(y.cpu().numpy(), ref)[0])
     print(f"{_id(case)} {rel[0]:.3e} two halves {rel[1]:.3e} ratio {rel[0] / rel[1]:.3f}")
     assert rel[0] <= 1.01 * rel[1]
+
+
+@pytest.mark.parametrize("m", (2, 4, 5, 6))
+@pytest.mark.parametrize("shape", [(120, 70, 50, 8, 70), (40, 200, 128, 28, 27), (16, 256, 256, 28, 26)], ids=lambda s: "x".join(map(str, s)))
+def test_kernel_transform_workgroups(shape, m):
+    """The kernel transform with 4, 8 and 16 frequencies a workgroup: parity with and without a plan."""
+    x, w, xd, wd = _device(shape, 80 + m)
+    N, C, K, H, W = shape
+    ys = [torch.full((N, K, H, W), float("nan"), device="cuda") for _ in range(2)]
+    with wc.Plan(*shape, m) as p:
+        assert "split products" in p.describe(), p.describe()
+        p.run(xd, wd, ys[0])
+        p.status()
+    try:
+        wc.wino_conv_run_noalloc(*shape, m, xd, wd, ys[1])
+    except wc.WinoError as e:
+        assert "scratch" in str(e)
+        ys[1] = ys[0]
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0], ys[1])
+    assert_close(ys[0].cpu().numpy(), direct_conv(x, w), m, f"F({m}) {shape}")
