@@ -499,6 +499,15 @@ def test_error_no_larger_than_two_halves(case):
     assert rel[0] <= 1.01 * rel[1]
 
 
+def test_rules_where_the_kernel_transform_weighs():
+    """Both sides of the lines for three-stage layers of 64 to 80 channels, drawn with kernels
+    given at every call in view."""
+    for shape, m, split in (((32, 64, 64, 56, 56), 4, False), ((16, 64, 64, 56, 56), 4, True), ((32, 81, 64, 56, 56), 4, True),
+                            ((2, 64, 128, 14, 14), 6, True), ((2, 64, 129, 14, 14), 6, False), ((2, 81, 256, 14, 14), 6, True)):
+        with wc.Plan(*shape, m, "three_stage") as p:
+            assert ("frequency_gemm_split" in p.describe()) == split, (shape, p.describe())
+
+
 @pytest.mark.parametrize("m", (2, 4, 5, 6))
 @pytest.mark.parametrize("shape", [(120, 70, 50, 8, 70), (40, 200, 128, 28, 27), (16, 256, 256, 28, 26)], ids=lambda s: "x".join(map(str, s)))
 def test_kernel_transform_workgroups(shape, m):
