@@ -651,8 +651,8 @@ bool fused_blocking_built(int m, int R, int kit) {
 //    tasks 67.8 -> 38.0; and from 32 (1/8) at 16 stages: 64 images of 7 x 7, 512
 //    channels, F(4) 64 tasks 114 -> 58; 16 of 14 x 14, 256 channels, F(4) 32 tasks
 //    39.5 -> 35.8; F(6) 40 tasks 53.4 -> 44.4.  Below, 8 to 28 tasks: 0.86-1.08 times.
-//  * F(2) from 48 (3/16): 2 images of 56 x 56, 64 channels, 49 tasks 12.7 -> 12.3; at
-//    25 0.73 times.
+//  * F(2) from 48 (3/16): 3 images of 56 x 56, 64 channels, 74 tasks 14.5 -> 12.9, at 49 12.4
+//    against 12.8 (12.3 before it added stages on their own, below), at 25 0.73 times.
 // Output channels that pad a task count as no work (K = 32, 98 half-empty tasks at F(4):
 // 0.79 times), F(5), whose gain is the smallest, takes at most a quarter of them (19
 // images of 56 x 56, C = 33, K = 65: 39.4 us against 42.0), and one stage of channels, C <= 16, is left to the fp32 kernel, whose
@@ -670,8 +670,46 @@ static bool split_enough(const Geometry &g, int num_cus) {
     if (M == 2 || si.n_tail == 0) return false;
     return (si.stages >= 6 && 4.0 * items > num_cus) || (si.stages >= 16 && 8.0 * items >= num_cus);
 }
+// Whether the fp32 kernel at its own blocking is the faster one although split_enough says
+// yes: it runs tasks of half the size, so that a layer may fill its rounds and leave half
+// of this kernel's units idle.  Times are estimated as rounds x (channel slope x channels +
+// output transform) + launch, in us, fitted to 74 layers of 32 to 512 channels that fill one
+// to four rounds of the fp32 kernel exactly (64 to 256 images of 32 x 32 at F(4), 32 to 128 of
+// 40 x 40 at F(5) and of 48 x 48 at F(6)); the estimates lie within 8%.  Rows that end inside
+// a tile cost the fp32 kernel its wide stores: 64 images of 32 x 30 at F(4) take 26.8 us for
+// 19.2, 32 of 40 x 37 at F(5) 23.3 for 20.4, of 48 x 46 and 48 x 45 at F(6) 27.6 and 34.4 for
+// 25.0; rows that are missing at the bottom cost it nothing.  Measured, one full round: F(4)
+// 64 channels 19.3 us against 24.1, F(5) 20.4 against 29.0, F(6) 25.0 against 36.2, 192
+// channels F(4) 44.0 -> 43.2, F(5) 41.9 against 46.5, F(6) 50.0 against 57.2; two: F(4) 64
+// channels 33.7 -> 28.2, F(5) 33.4 -> 31.0, F(6) 41.5 -> 39.6; three: F(4) 32 channels 27.6 against
+// 31.3, F(5) 64 46.5 against 51.7, F(6) 57.4 against 66.7; many: 32 channels, 512 of 48 x 48
+// F(6) 159 against 168, 17 channels, 1 of 2040 x 2040 F(4) 1040 against 1108.  F(2): one full round of tasks
+// smaller than this kernel's, 8 images of 32 x 32, 64 channels 8.9 against 12.6, 160 channels
+// 15.7 against 16.4, 192 17.3 -> 16.8.
+static bool fp32_rounds_better(const Geometry &g, int num_cus) {
+    const FusedCfg f = fused_cfg_default(g, num_cus, FusedKernel::kFp32);
+    const SplitInfo si = fused_split_info(g, FusedCfg{0, 0, num_cus, 0, true, false});
+    const int items = fused_split_info(g, f).n_items;
+    if (g.m == 2) return items == num_cus && f.R * f.kit < 32 * 64 && si.stages <= 11;
+    if (f.kit != (g.m == 4 ? 64 : 32)) return false;
+    struct Cost {
+        double slope, round, launch, piece, part;  // part: share of a round that a last one of whole items takes
+    };
+    const Cost cf = g.m == 4 ? Cost{0.196, 1.9, 4.8, 0, 1} : g.m == 5 ? Cost{0.183, 1.5, 7.0, 0, 1} : Cost{0.203, 3.1, 8.7, 0, 1};
+    const Cost cs = g.m == 4   ? Cost{0.240, 9.5, 3.0, 7.7, 0.8}
+                    : g.m == 5 ? Cost{0.288, 5.9, 6.5, 6.4, 0.85}
+                               : Cost{0.333, 10.0, 8.0, 7.0, 0.85};
+    const double C = 16.0 * si.stages, rounds = (items + num_cus - 1) / num_cus;
+    const double ragged = g.W % g.m == 0 ? 0 : g.m == 4 ? 7.0 : g.m == 5 ? 2.9 : g.W % 2 == 0 ? 2.6 : 10.0;
+    const double tf = cf.launch + rounds * (cf.slope * C + cf.round + ragged);
+    const int tail = si.n_items % num_cus;
+    double ts = cs.launch + si.nfull * (cs.slope * C + cs.round);
+    if (si.n_tail > 0) ts += cs.slope * 16.0 * si.piece + cs.round + cs.piece;
+    else if (tail > 0) ts += (2 * tail <= num_cus ? cs.part : 1.0) * (cs.slope * C + cs.round);
+    return tf < 0.96 * ts;
+}
 static bool split_fits(const Geometry &g, int num_cus) {
-    if (!split_possible(g)) return false;
+    if (!split_possible(g) || fp32_rounds_better(g, num_cus)) return false;
 #define WINO_SPLIT_ENOUGH(m_) \
     if (g.m == m_) return split_enough<m_>(g, num_cus);
     WINO_SPLIT_M(WINO_SPLIT_ENOUGH)

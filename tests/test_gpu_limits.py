@@ -55,3 +55,19 @@ def test_largest_accepted_sizes(case):
     del y, xd, wd
     torch.cuda.empty_cache()
     assert_close(got, ref, m, f"{case} planes {planes}")
+
+
+SPLIT_Y_LIMIT = (1, 64, 128, 2040, 2040)
+SPLIT_X_LIMIT = (1, 128, 64, 2040, 2040)
+
+
+@pytest.mark.parametrize("shape,m", [(SPLIT_Y_LIMIT, 2), (SPLIT_Y_LIMIT, 4), (SPLIT_Y_LIMIT, 5), (SPLIT_Y_LIMIT, 6),
+                                     (SPLIT_X_LIMIT, 2), (SPLIT_X_LIMIT, 5)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else f"m{v}")
+def test_split_kernel_at_the_largest_sizes(shape, m):
+    """The same limits on the split-product kernel, which takes layers of more than 16
+    channels: the stores of its epilogue at the largest offsets of y, and the loads of F(2)
+    and F(5) at the largest of x."""
+    with wc.Plan(*shape, m) as p:
+        assert "split products" in p.describe(), p.describe()
+    test_largest_accepted_sizes((shape, m, "fused"))

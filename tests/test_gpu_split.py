@@ -527,3 +527,18 @@ def test_kernel_transform_workgroups(shape, m):
     torch.cuda.synchronize()
     assert torch.equal(ys[0], ys[1])
     assert_close(ys[0].cpu().numpy(), direct_conv(x, w), m, f"F({m}) {shape}")
+
+
+@pytest.mark.parametrize("shape,m,split", [
+    ((64, 64, 64, 32, 32), 4, False), ((63, 64, 64, 32, 32), 4, True), ((65, 64, 64, 32, 32), 4, True),
+    ((64, 64, 64, 32, 30), 4, True), ((64, 64, 64, 30, 32), 4, False), ((64, 256, 64, 32, 32), 4, True), ((128, 64, 64, 32, 32), 4, True),
+    ((192, 32, 64, 32, 32), 4, False), ((32, 64, 64, 40, 40), 5, False), ((32, 512, 64, 40, 40), 5, True),
+    ((96, 64, 64, 40, 40), 5, False), ((32, 64, 64, 48, 48), 6, False), ((32, 64, 64, 47, 46), 6, False), ((32, 128, 64, 47, 45), 6, True), ((64, 64, 64, 48, 48), 6, True),
+    ((8, 64, 64, 32, 32), 2, False), ((16, 64, 64, 32, 32), 2, False), ((32, 64, 64, 32, 32), 2, True),
+    ((2, 192, 64, 64, 64), 2, True), ((9, 64, 64, 32, 32), 2, True)], ids=str)
+def test_full_rounds_of_the_fp32_kernel(shape, m, split):
+    """Layers that fill rounds of the fp32 kernel's smaller tasks stay on it; their neighbours
+    in images, channels and raggedness on the split-product kernel (256 compute units)."""
+    assert torch.cuda.get_device_properties(0).multi_processor_count == 256
+    with wc.Plan(*shape, m) as p:
+        assert ("split products" in p.describe()) == split, p.describe()
