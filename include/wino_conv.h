@@ -112,8 +112,8 @@ enum {
  * at least one task per compute unit; otherwise the blocking with the most
  * tasks.  wino_conv_plan_tuned measures every blocking and both kernels
  * instead.  wino_conv_describe
- * names the kernel a plan runs.  The split-product kernel's results are those of the fp32 kernel to fp32
- * rounding over the whole range of float: values are multiplied at a scale that keeps
+ * names the kernel a plan runs.  The split-product kernel's results are those of the
+ * fp32 kernel to fp32 rounding over the whole range of float: values are multiplied at a scale that keeps
  * all terms of the smallest, denormal ones included, and output tiles whose sums
  * leave the scaled range (transformed values of 2^102 and more, sums of products of
  * 2^80 and more, infinities, NaNs) are computed again as fp32 products, which takes
@@ -130,9 +130,11 @@ typedef struct {
 /* Create a plan for an F(m x m, 3 x 3) convolution of an N x C x H x W input
  * with K output channels, on the current HIP device, with the fused algorithm
  * and automatic blocking.  Allocates the plan's device workspace: the
- * transformed kernels (T^2 * C * K floats rounded up to the blocking) and, when
- * the last round of work items is split across compute units, their partial
- * outputs and arrival counters (zeroed here; every call leaves them zero).
+ * transformed kernels (T^2 * C * K floats rounded up to the blocking; for split
+ * products 6 bytes a value with C rounded up to 16 and K to 64: 1.4
+ * to 2.4 times the floats) and, when the last round of work items is split across
+ * compute units, their partial outputs (at most one per compute unit: 38 MB on 256)
+ * and arrival counters (zeroed here; every call leaves them zero).
  * Returns NULL (see wino_last_error) if a size is < 1, m is not 2, 4, 5 or 6 (also 7
  * for WINO_ALGO_THREE_STAGE; 14 for WINO_ALGO_FFT, which takes no other m), a
  * size overflows the 32-bit offsets the kernels use (each of x and y must be
@@ -143,9 +145,11 @@ wino_plan *wino_conv_plan(int N, int C, int K, int H, int W, int m);
  * overrides (t may be NULL; they apply to WINO_ALGO_FUSED and are ignored by the
  * others, except that channel_splits > 1 is refused for them).  The
  * three-stage plan also allocates its intermediate buffers (T^2 * tiles * (C + K)
- * floats, rounded up to the blocking); the FFT plan's transformed kernels take
- * 144 * 16 bytes per (input, output) channel pair, padded to multiples of 4 and
- * 16. */
+ * floats, rounded up to the blocking; transformed kernels as above); the FFT plan's
+ * transformed kernels take 144 * 16 bytes per (input, output) channel pair, padded to
+ * multiples of 4 and 16, and where a round of its items is cut into pieces their
+ * partial outputs take 200704 bytes a piece, at most two per compute unit (103 MB on
+ * 256), with arrival counters beside them. */
 wino_plan *wino_conv_plan_ex(int N, int C, int K, int H, int W, int m, int algo,
                              const wino_tuning *t);
 
@@ -175,8 +179,9 @@ int wino_conv_run_pretransformed(const wino_plan *p, const float *x, float *y, v
  * partial outputs and arrival counters -- lives in a file-scope device array, one
  * per GPU, held until the process ends.  A layer is accepted when that scratch,
  * counted at 4 bytes per transformed kernel value, fits
- * WINO_NOALLOC_SCRATCH_BYTES (the array itself is 5 times that: the
- * split-product kernels hold a value in 6 bytes and have larger partial outputs).  The
+ * WINO_NOALLOC_SCRATCH_BYTES (the array itself is 5 times that, 80 MiB on each GPU of
+ * each process that loads the library: the split-product kernels hold a value in 6
+ * bytes and have larger partial outputs).  The
  * counters are cleared by the kernel transform at every call (no memset).
  * Every call on a GPU shares that GPU's array and leaves its own contents in it:
  * calls that overlap on one GPU (different streams or threads) race and give

@@ -107,10 +107,12 @@ extern "C" int wino_conv_run_noalloc(int N, int C, int K, int H, int W, int m, c
     const size_t off_cnt = kAlign, off_part = off_cnt + align_up(cnt_bytes);
     const size_t off_wt = off_part + align_up(part_bytes);
     const size_t total = off_wt + align_up(cfg.split ? wino::split_weight_bytes(g) : wt_bytes);
-    if (counted > kScratchBytes || total > kArrayBytes) {
+    if (counted > kScratchBytes || total > kArrayBytes) {  // the second does not happen (kArrayBytes)
+        const bool past = counted > kScratchBytes;
         wino::set_error("this layer needs %zu bytes of scratch (transformed kernels %zu), wino_conv_run_noalloc holds "
                         "%zu; use a plan (wino_conv_plan) instead",
-                        counted, wt_bytes, kScratchBytes);
+                        past ? counted : total, past || !cfg.split ? wt_bytes : wino::split_weight_bytes(g),
+                        past ? kScratchBytes : kArrayBytes);
         return WINO_EUNSUPPORTED;
     }
     hipStream_t s = static_cast<hipStream_t>(stream);
