@@ -642,9 +642,9 @@ bool fused_blocking_built(int m, int R, int kit) {
 // to four times the fp32 kernel's, so a layer needs enough of them.  Measured against
 // the fp32 kernel (us per call, C = K):
 //  * F(4) to F(6) from 80 tasks (5/16 of the compute units): F(4) 40 images of 14 x
-//    14, 256 channels, 80 tasks 80.4 -> 45.6, 32 of 224 x 224, 64 channels 373 -> 317;
-//    F(5) 32 of 28 x 28, 256 channels, 288 tasks 148 -> 122; F(6) 32 of 112 x 112, 128
-//    channels, 1444 tasks 405 -> 365.  At 50 tasks of 4 or 8 stages 0.64-0.94 times as
+//    14, 256 channels, 80 tasks 80.4 -> 45.6, 32 of 224 x 224, 64 channels 373 -> 313;
+//    F(5) 32 of 28 x 28, 256 channels, 288 tasks 148 -> 127; F(6) 32 of 112 x 112, 128
+//    channels, 1444 tasks 405 -> 374.  At 50 tasks of 4 or 8 stages 0.64-0.94 times as
 //    fast, as the fp32 kernel's smaller tasks then fit one round.
 //  * Tasks cut into pieces from more than 64 (1/4) at 6 stages: F(5) 16 images of 28 x
 //    28, 128 channels, 72 tasks 48.1 -> 36.0, F(6) 4 of 75 x 53, C = 96, K = 160, 75
@@ -655,9 +655,9 @@ bool fused_blocking_built(int m, int R, int kit) {
 //    against 12.8 (12.3 before it added stages on their own, below), at 25 0.73 times.
 // Output channels that pad a task count as no work (K = 32, 98 half-empty tasks at F(4):
 // 0.79 times), F(5), whose gain is the smallest, takes at most a quarter of them (19
-// images of 56 x 56, C = 33, K = 65: 39.4 us against 42.0), and one stage of channels, C <= 16, is left to the fp32 kernel, whose
-// task has the shorter epilogue (32 images of 112 x 112, C = 3, K = 64: 37.6 us against
-// 41.7).  The transformed kernels take up to 2.4 times the fp32 kernel's (6 bytes a
+// images of 56 x 56, C = 33, K = 65: 39.4 us against 42.0), and one stage of channels,
+// C <= 16, is left to the fp32 kernel, whose task has the shorter epilogue (32 images of
+// 112 x 112, C = 3, K = 64: 37.6 us against 41.7).  The transformed kernels take up to 2.4 times the fp32 kernel's (6 bytes a
 // value, channels padded to 16); those of one task are addressed with 32-bit byte
 // offsets, which 64 output channels at F(4) exceed from 310,000 input channels on.
 template <int M>
@@ -683,9 +683,9 @@ static bool split_enough(const Geometry &g, int num_cus) {
 // channels F(4) 44.0 -> 43.2, F(5) 41.9 against 46.5, F(6) 50.0 against 57.2; two: F(4) 64
 // channels 33.7 -> 28.2, F(5) 33.4 -> 31.0, F(6) 41.5 -> 39.6; three: F(4) 32 channels 27.6 against
 // 31.3, F(5) 64 46.5 against 51.7, F(6) 57.4 against 66.7; many: 32 channels, 512 of 48 x 48
-// F(6) 159 against 168, 17 channels, 1 of 2040 x 2040 F(4) 1040 against 1108.  F(2): one full round of tasks
-// smaller than this kernel's, 8 images of 32 x 32, 64 channels 8.9 against 12.6, 160 channels
-// 15.7 against 16.4, 192 17.3 -> 16.8.
+// F(6) 159 against 168, 17 channels, 1 of 2040 x 2040 F(4) 1040 against 1108.  F(2): one
+// full round of tasks smaller than this kernel's, 8 images of 32 x 32, 64 channels 8.9
+// against 12.6, 160 channels 15.7 against 16.4, 192 17.3 -> 16.8.
 static bool fp32_rounds_better(const Geometry &g, int num_cus) {
     const FusedCfg f = fused_cfg_default(g, num_cus, FusedKernel::kFp32);
     const SplitInfo si = fused_split_info(g, FusedCfg{0, 0, num_cus, 0, true, false});
@@ -695,7 +695,9 @@ static bool fp32_rounds_better(const Geometry &g, int num_cus) {
     struct Cost {
         double slope, round, launch, piece, part;  // part: share of a round that a last one of whole items takes
     };
-    const Cost cf = g.m == 4 ? Cost{0.196, 1.9, 4.8, 0, 1} : g.m == 5 ? Cost{0.183, 1.5, 7.0, 0, 1} : Cost{0.203, 3.1, 8.7, 0, 1};
+    const Cost cf = g.m == 4   ? Cost{0.196, 1.9, 4.8, 0, 1}
+                    : g.m == 5 ? Cost{0.183, 1.5, 7.0, 0, 1}
+                               : Cost{0.203, 3.1, 8.7, 0, 1};
     const Cost cs = g.m == 4   ? Cost{0.240, 9.5, 3.0, 7.7, 0.8}
                     : g.m == 5 ? Cost{0.288, 5.9, 6.5, 6.4, 0.85}
                                : Cost{0.333, 10.0, 8.0, 7.0, 0.85};
