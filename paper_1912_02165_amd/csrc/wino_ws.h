@@ -830,6 +830,17 @@ inline bool item_order_kernels_first(const Geometry &g, int n_kgroups) {
     return n_kgroups > 1 && (double)g.T2 * g.C * g.K > (double)g.N * g.C * g.H * g.W;
 }
 
+// Whether y is stored streaming (kStreamOutputBytes).  Not at F(6) where every tile is whole
+// but rows are no multiple of 32 bytes: there the parts of a line that two waves store on
+// their own reach memory apart (150 MiB of y, C = K = 64, split products, streaming / not: 42 x
+// 42 200 / 184 us, 150 x 150 157 / 138, K = 96 222 / 218, 102 x 102 189 / 186; fp32 kernel C = 16
+// 150 x 150 89 / 61; at rows of 32 bytes 168 x 168 178 / 185, and with clipped tiles, most
+// of which are not streamed anyway, 152 x 152 141 / 153).
+template <int M>
+bool stream_output(const Geometry &g) {
+    return (long long)g.N * g.K * g.H * g.W * 4 >= kStreamOutputBytes && (M != 6 || g.W % M != 0 || g.W % 8 == 0);
+}
+
 // Launch of one instantiation; returns the launch status.
 template <int M, int TB, int FS, int CSP>
 hipError_t launch_ws_t(const Geometry &g, const float *x, const float *wt, float *y, bool vec, int num_cus,
@@ -852,7 +863,7 @@ hipError_t launch_ws_t(const Geometry &g, const float *x, const float *wt, float
     const bool vx = (reinterpret_cast<uintptr_t>(x) % vw == 0) && ((unsigned)g.W * 4u) % vw == 0;
     const bool km = item_order_kernels_first(g, si.n_kgroups);
     const int n_inner = km ? si.n_items / si.n_kgroups : si.n_kgroups;
-    const int ystream = (long long)g.N * g.K * g.H * g.W * 4 >= kStreamOutputBytes ? 1 : 0;
+    const int ystream = stream_output<M>(g) ? 1 : 0;
     auto go = [&](auto kern) {
         hipLaunchKernelGGL(kern, grid, block, 0, s, x, reinterpret_cast<const floatx4 *>(wt), y, g, vec ? 1 : 0,
                            n_inner, si.n_items, sp, ystream);
