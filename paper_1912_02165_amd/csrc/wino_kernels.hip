@@ -910,22 +910,27 @@ hipError_t launch_frequency_gemm_split(const Geometry &g, const float *U, const 
 
 // With few channels the pipeline is bound by U and M in memory, a step of 16 channels is
 // partly padding and M is written in 8-byte halves: measured against the fp32 products
-// 0.84-0.98 times as fast at C <= 32, 1.00-1.52 times above 80 channels (whole pipelines,
+// 0.84-0.98 times as fast at C <= 32, 1.00-1.52 times from 80 channels on (whole pipelines,
 // F(2) to F(7), 1 to 64 images, kernels ahead of time: the 14x14 C = K = 512 layer at F(7)
-// 152 -> 121 us, 7x7 C = K = 512 N = 64 at F(4) 94.2 -> 61.9).  Between, 64 to 80 channels
-// gain 0 to 8% (14x14 C = 80, K = 200 N = 8 F(4) 18.6 -> 17.2), except where
-//  * U and M leave the caches: 56x56 C = K = 64 N = 32, 115 MB at F(4), 55.3 against 58 us,
-//    115 at F(5) 57.7 against 59.7, 105 at F(6) 57.0 against 58.8 (N = 16 F(4) 33.3 -> 32.0);
-//  * kernels are given at every call and are many, as their transform takes longer (6 bytes
-//    a value): C = 64, K = 256 14x14 N = 2 F(7) 24.4 against 25.4, C = 70, K = 200 30x30 N = 8
-//    F(6) 30.5 against 31.6 (C = 64, K = 128 28x28 N = 8 F(6) 26.4 -> 26.0).
+// 152 -> 121 us, 7x7 C = K = 512 N = 64 at F(4) 94.2 -> 61.9, 56x56 C = 80, K = 256 N = 16 F(6)
+// 83.2 -> 78.1).  Between, 64 to 79 channels gain 0 to 8%, except where
+//  * U and M leave the caches and few output channels reuse them: 56x56 C = K = 64 N = 32,
+//    115 MB at F(4), 55.3 against 58 us, 115 at F(5) 57.0 against 57.5, 105 at F(6) 57.0
+//    against 58.8 (N = 16 F(4) 33.3 -> 32.0; K = 256 N = 32 F(4) 193.9 -> 190.1);
+//  * kernels are given at every call and are many for their products, as their transform
+//    takes longer (6 bytes a value): C = 64, K = 256 14x14 N = 2 F(7) 24.4 against 25.3, C = 70,
+//    K = 200 30x30 N = 8 F(6) 30.5 against 31.6, C = 72, K = 256 28x28 N = 8 F(4), 2.6e8
+//    products, 30.2 against 31.3 (C = 64, K = 512 F(6), 4.2e8, 44.9 -> 41.2, 40x40 N = 16 F(4),
+//    1.9e9, 81.1 -> 78.2; C = 64, K = 128 28x28 N = 8 F(6) 26.4 -> 26.0).
 // F(7) layers of more than 256 x 256 channels keep the fp32 products up to 128 tiles, where
 // the transform of the largest kernels weighs most: with kernels given 14x14 C = K = 512 N = 1
 // measured 78.2 against 94.7 us, and 77.3 against 75.6 with the transform as it is now, C =
 // 256, K = 512 52.8 against 54.0; kernels ahead of time would gain there (59.1 -> 47.4).
 bool three_stage_split(const Geometry &g) {
     if (g.C < 64 || (g.m == 7 && g.tiles_p <= 128 && (long long)g.C * g.K > 256 * 256)) return false;
-    return g.C > 80 || (g.K <= 2 * g.C && (double)g.T2 * g.tiles_p * (g.C + g.K) * sizeof(float) <= 96e6);
+    if (g.C >= 80) return true;
+    if (g.K > 2 * g.C) return (double)g.T2 * g.tiles_p * g.C * g.K >= 3e8;
+    return (double)g.T2 * g.tiles_p * (g.C + g.K) * sizeof(float) <= 96e6;
 }
 
 hipError_t launch_output_transform(const Geometry &g, const float *Min, float *y, hipStream_t s) {

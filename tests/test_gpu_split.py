@@ -503,7 +503,8 @@ def test_rules_where_the_kernel_transform_weighs():
     """Both sides of the lines for three-stage layers of 64 to 80 channels, drawn with kernels
     given at every call in view."""
     for shape, m, split in (((32, 64, 64, 56, 56), 4, False), ((16, 64, 64, 56, 56), 4, True), ((32, 81, 64, 56, 56), 4, True),
-                            ((2, 64, 128, 14, 14), 6, True), ((2, 64, 129, 14, 14), 6, False), ((2, 81, 256, 14, 14), 6, True)):
+                            ((2, 64, 128, 14, 14), 6, True), ((2, 64, 129, 14, 14), 6, False), ((2, 80, 256, 14, 14), 6, True),
+                            ((8, 64, 512, 28, 28), 6, True), ((8, 72, 256, 28, 28), 4, False), ((32, 64, 256, 56, 56), 4, True)):
         with wc.Plan(*shape, m, "three_stage") as p:
             assert ("frequency_gemm_split" in p.describe()) == split, (shape, p.describe())
 
