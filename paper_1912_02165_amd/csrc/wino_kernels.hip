@@ -685,7 +685,11 @@ static bool split_enough(const Geometry &g, int num_cus) {
 // 31.3, F(5) 64 46.5 against 51.7, F(6) 57.4 against 66.7; many: 32 channels, 512 of 48 x 48
 // F(6) 159 against 168, 17 channels, 1 of 2040 x 2040 F(4) 1040 against 1108.  F(2): one
 // full round of tasks smaller than this kernel's, 8 images of 32 x 32, 64 channels 8.9
-// against 12.6, 160 channels 15.7 against 16.4, 192 17.3 -> 16.8.
+// against 12.6, 160 channels 15.7 against 16.4, 192 17.3 -> 16.8.  F(5) and F(6) outputs of
+// 128 MiB and more in whole tiles whose rows are no multiple of 32 and 64 bytes cost this
+// kernel, which has more stores in flight, a further 3 and 5 a round: C = K = 64, 304 images of
+// 45 x 45 F(5) 179 against 194, 60 of 102 x 102 F(6) 171 against 186, 22 of 168 x 168 155
+// against 176; aligned 24 of 160 x 160 F(5) 161 -> 141, 67 of 96 x 96 F(6) 149 -> 148.
 static bool fp32_rounds_better(const Geometry &g, int num_cus) {
     const FusedCfg f = fused_cfg_default(g, num_cus, FusedKernel::kFp32);
     const SplitInfo si = fused_split_info(g, FusedCfg{0, 0, num_cus, 0, true, false});
@@ -704,10 +708,12 @@ static bool fp32_rounds_better(const Geometry &g, int num_cus) {
     const double C = 16.0 * si.stages, rounds = (items + num_cus - 1) / num_cus;
     const double ragged = g.W % g.m == 0 ? 0 : g.m == 4 ? 7.0 : g.m == 5 ? 2.9 : g.W % 2 == 0 ? 2.6 : 10.0;
     const double tf = cf.launch + rounds * (cf.slope * C + cf.round + ragged);
+    const bool large = (long long)g.N * g.K * g.H * g.W * 4 >= kStreamOutputBytes && g.W % g.m == 0;
+    const double round = cs.round + (!large ? 0 : g.m == 5 && g.W % 8 != 0 ? 3.0 : g.m == 6 && g.W % 16 != 0 ? 5.0 : 0);
     const int tail = si.n_items % num_cus;
-    double ts = cs.launch + si.nfull * (cs.slope * C + cs.round);
-    if (si.n_tail > 0) ts += cs.slope * 16.0 * si.piece + cs.round + cs.piece;
-    else if (tail > 0) ts += (2 * tail <= num_cus ? cs.part : 1.0) * (cs.slope * C + cs.round);
+    double ts = cs.launch + si.nfull * (cs.slope * C + round);
+    if (si.n_tail > 0) ts += cs.slope * 16.0 * si.piece + round + cs.piece;
+    else if (tail > 0) ts += (2 * tail <= num_cus ? cs.part : 1.0) * (cs.slope * C + round);
     return tf < 0.96 * ts;
 }
 static bool split_fits(const Geometry &g, int num_cus) {

@@ -57,7 +57,7 @@ def test_largest_accepted_sizes(case):
     assert_close(got, ref, m, f"{case} planes {planes}")
 
 
-SPLIT_Y_LIMIT = (1, 64, 128, 2040, 2040)
+SPLIT_Y_LIMIT = (1, 64, 128, 2039, 2041)   # whole and clipped tiles in a row
 SPLIT_X_LIMIT = (1, 128, 64, 2040, 2040)
 
 

@@ -536,7 +536,9 @@ def test_kernel_transform_workgroups(shape, m):
     ((192, 32, 64, 32, 32), 4, False), ((32, 64, 64, 40, 40), 5, False), ((32, 512, 64, 40, 40), 5, True),
     ((96, 64, 64, 40, 40), 5, False), ((32, 64, 64, 48, 48), 6, False), ((32, 64, 64, 47, 46), 6, False), ((32, 128, 64, 47, 45), 6, True), ((64, 64, 64, 48, 48), 6, True),
     ((8, 64, 64, 32, 32), 2, False), ((16, 64, 64, 32, 32), 2, False), ((32, 64, 64, 32, 32), 2, True),
-    ((2, 192, 64, 64, 64), 2, True), ((9, 64, 64, 32, 32), 2, True)], ids=str)
+    ((2, 192, 64, 64, 64), 2, True), ((9, 64, 64, 32, 32), 2, True),
+    ((304, 64, 64, 45, 45), 5, False), ((24, 64, 64, 160, 160), 5, True), ((60, 64, 64, 102, 102), 6, False),
+    ((67, 64, 64, 96, 96), 6, True)], ids=str)
 def test_full_rounds_of_the_fp32_kernel(shape, m, split):
     """Layers that fill rounds of the fp32 kernel's smaller tasks stay on it; their neighbours
     in images, channels and raggedness on the split-product kernel (256 compute units)."""
